@@ -11,6 +11,7 @@
 //                   rescale of O are per-lane and P feeds the second product
 //                   straight from registers. K/V tiles stream through padded
 //                   LDS rows (conflict-free for both access patterns).
+//   k_attn_ksplit   bf16, hd 128, few rows per kv-head (also GQA decode): four waves split the keys.
 //   k_attn_decode   one query per sequence: a bandwidth-bound stream over the
 //                   K/V caches with 16-byte loads, dot products reduced across
 //                   the lanes of one key row, and an online softmax.
@@ -25,6 +26,7 @@
 
 #include <math.h>
 
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 
@@ -920,6 +922,13 @@ __global__ __launch_bounds__(pp::NWAVE * 64, 1) void k_attn_pp(AttnArgs a, int r
 
 // ------------------------------------------------------------------ key-split prefill (bf16)
 //
+// DEC: one query per sequence and a GQA group of up to 16 heads. Columns 0..15 and 16..31 of the
+// score product hold the same query rows, so both halves form the same probabilities; the first half
+// multiplies V by their bf16 values and the second by what that rounding left over, and the two
+// outputs are added at the end: O as with fp32 probabilities, from MFMAs that the 32-column product
+// spends anyway. Bound by the caches' bytes: 28 query heads over 4 kv-heads, 16585 keys a sequence,
+// 92 us a layer for B 16 (5.9 TB/s) where the VALU decode kernel took 339 us.
+//
 // For few query rows per (batch, kv-head) (LLaVA: 64) one block of four waves takes 32 rows
 // and every wave streams a quarter of the 32-key tiles through its own two LDS stages, so all
 // four SIMDs of the CU work and no barrier is needed until the waves merge their partial
@@ -941,6 +950,7 @@ constexpr int MPITCH = HD + 4;              // merge rows padded by 16 B: rows f
 static_assert(NWAVE * 32 * (MPITCH + 2) * 4 <= LDS_BYTES, "merge buffer must fit");
 }  // namespace ksplit
 
+template <bool DEC>
 __global__ __launch_bounds__(ksplit::NWAVE * 64) void k_attn_ksplit(AttnArgs a, int row_blocks) {
   using namespace ksplit;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -951,7 +961,8 @@ __global__ __launch_bounds__(ksplit::NWAVE * 64) void k_attn_ksplit(AttnArgs a, 
   const int rb = wk.rb, bg = wk.bg, split = wk.split;
   const int b = uni(bg / a.Hkv), g = bg - b * a.Hkv;
   const int row0 = rb * 32;
-  const int my_row = row0 + (lane & 31);
+  const int my_row = DEC ? lane & 15 : row0 + (lane & 31);
+  const bool low = DEC && (lane & 16) != 0;  // this lane's P V product takes the low parts of P
   const bool row_ok = my_row < R;
   const int my_i = row_ok ? my_row / G : 0;
   const int my_h = g * G + (row_ok ? my_row - my_i * G : 0);
@@ -1063,7 +1074,11 @@ __global__ __launch_bounds__(ksplit::NWAVE * 64) void k_attn_ksplit(AttnArgs a, 
     for (int s2 = 0; s2 < 2; ++s2) {
       bf16x8 pf;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) pf[e] = (bf16)sacc[0][s2 * 8 + e];
+      for (int e = 0; e < 8; ++e) {
+        const float p = sacc[0][s2 * 8 + e];
+        pf[e] = (bf16)p;
+        if (DEC) pf[e] = low ? (bf16)(p - (float)pf[e]) : pf[e];
+      }
       lsum[s2] = add_probs(pf, lsum[s2]);
 #pragma unroll
       for (int cb = 0; cb < HD / 32; ++cb) {
@@ -1078,7 +1093,8 @@ __global__ __launch_bounds__(ksplit::NWAVE * 64) void k_attn_ksplit(AttnArgs a, 
     if (t + 2 * NWAVE < t_end) issue(t + 2 * NWAVE, stage);
     stage ^= 1;
   }
-  const float l_mine = l_run + shfl_xor(l_run, 32);
+  float l_mine = l_run + shfl_xor(l_run, 32);
+  if (DEC) l_mine += shfl_xor(l_mine, 16);
 
   // Merge the four key groups: every wave publishes (m, l, O^T) and wave w finishes columns
   // 32w .. 32w + 31 of the block's 32 rows.
@@ -1112,7 +1128,7 @@ __global__ __launch_bounds__(ksplit::NWAVE * 64) void k_attn_ksplit(AttnArgs a, 
     sc[w] = __builtin_amdgcn_exp2f(red_ml[(w * 32 + rrow) * 2] - mx);
     lt += red_ml[(w * 32 + rrow) * 2 + 1] * sc[w];
   }
-  if (!row_ok) return;
+  if (!row_ok || low) return;
   const int64_t orow = ((int64_t)b * a.Nq + my_i) * a.Hq + my_h;
   const int cbase = wave * 32 + g2 * 16;  // this lane's 16 columns
   float out[16];
@@ -1123,7 +1139,8 @@ __global__ __launch_bounds__(ksplit::NWAVE * 64) void k_attn_ksplit(AttnArgs a, 
     const float* o = red_o + (w * 32 + rrow) * MPITCH + cbase;
 #pragma unroll
     for (int e4 = 0; e4 < 4; ++e4) {
-      const f32x4 v = *(const f32x4*)(o + e4 * 4);
+      f32x4 v = *(const f32x4*)(o + e4 * 4);
+      if (DEC) v += *(const f32x4*)(o + 16 * MPITCH + e4 * 4);
 #pragma unroll
       for (int u = 0; u < 4; ++u) out[e4 * 4 + u] += v[u] * sc[w];
     }
@@ -1320,29 +1337,75 @@ __global__ __launch_bounds__(256) void k_attn_decode(AttnArgs a) {
 
 // ------------------------------------------------------------------ combine
 
-template <typename T, int HD>
+// SG groups of CPR threads share a row: group q takes the splits q, q + SG, ... and the groups'
+// (max, sum, O) meet in LDS, always in the same order. A group loads the partial rows together with
+// their (max, sum), so the kernel waits for memory once, not once for the maxima and again for the
+// rows: the partials come from other XCDs' blocks, from beyond this XCD's L2.
+template <typename T, int HD, int SG>
 __global__ __launch_bounds__(256) void k_attn_combine(const float* __restrict__ Opart,
                                                       const float* __restrict__ MLpart,
                                                       T* __restrict__ O, int64_t rows, int splits) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  constexpr int CPR = HD / 4;
-  if (t >= rows * CPR) return;
-  const int64_t row = t / CPR;
-  const int c = (int)(t - row * CPR) * 4;
-  // Unrolled so that several splits' loads are in flight at once: the partials were written by
-  // blocks on every XCD and come from beyond this XCD's L2.
-  float mx = NEG_BIG;
-#pragma unroll 8
-  for (int s = 0; s < splits; ++s) mx = fmaxf(mx, MLpart[((int64_t)s * rows + row) * 2]);
-  float lt = 0.f;
+  constexpr int CPR = HD / 4, SLOTS = 256 / CPR, U = 4;
+  __shared__ float red[SG > 1 ? SLOTS : 1][HD + 4];  // a slot's O (HD values), max and sum
+  const int slot = threadIdx.x / CPR, c = (threadIdx.x % CPR) * 4, grp = slot % SG;
+  const int64_t row = (int64_t)blockIdx.x * (SLOTS / SG) + slot / SG;
+  const bool row_ok = row < rows;
+  float mx = NEG_BIG, lt = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-  for (int s = 0; s < splits; ++s) {
-    const float* ml = MLpart + ((int64_t)s * rows + row) * 2;
-    const float sc = exp2f(ml[0] - mx);
-    lt += ml[1] * sc;
-    acc += *(const f32x4*)(Opart + ((int64_t)s * rows + row) * HD + c) * sc;
+  if (row_ok) {
+    for (int s0 = grp; s0 < splits; s0 += SG * U) {
+      float m[U], l[U];
+      f32x4 o[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int s = s0 + u * SG;
+        m[u] = NEG_BIG;
+        l[u] = 0.f;
+        o[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (s < splits) {
+          const f32x2 ml = *(const f32x2*)(MLpart + ((int64_t)s * rows + row) * 2);
+          m[u] = ml[0];
+          l[u] = ml[1];
+          o[u] = *(const f32x4*)(Opart + ((int64_t)s * rows + row) * HD + c);
+        }
+      }
+      float mn = mx;
+#pragma unroll
+      for (int u = 0; u < U; ++u) mn = fmaxf(mn, m[u]);
+      const float a = exp2f(mx - mn);
+      mx = mn;
+      lt *= a;
+      acc *= a;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const float sc = exp2f(m[u] - mx);
+        lt += l[u] * sc;
+        acc += o[u] * sc;
+      }
+    }
   }
+  if constexpr (SG > 1) {
+    *(f32x4*)&red[slot][c] = acc;
+    if (c == 0) {
+      red[slot][HD] = mx;
+      red[slot][HD + 1] = lt;
+    }
+    __syncthreads();
+    if (grp != 0) return;
+    float mn = mx;
+#pragma unroll
+    for (int q = 1; q < SG; ++q) mn = fmaxf(mn, red[slot + q][HD]);
+    const float a = exp2f(mx - mn);
+    lt *= a;
+    acc *= a;
+#pragma unroll
+    for (int q = 1; q < SG; ++q) {
+      const float sc = exp2f(red[slot + q][HD] - mn);
+      lt += red[slot + q][HD + 1] * sc;
+      acc += *(const f32x4*)&red[slot + q][c] * sc;
+    }
+  }
+  if (!row_ok) return;
   const float inv = lt > 0.f ? 1.f / lt : 0.f;
   store4<T>(O + row * HD + c, acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
 }
@@ -1350,6 +1413,34 @@ __global__ __launch_bounds__(256) void k_attn_combine(const float* __restrict__ 
 // ------------------------------------------------------------------ host side
 
 static inline int64_t cdiv64(int64_t x, int64_t y) { return (x + y - 1) / y; }
+
+// Key splits of the key-split kernel, from its time on MI355X in us: 1.12 per step in which a block's
+// four waves take a 32-key tile each (latency-bound: 64 KiB a CU), joined with the caches' bytes at
+// 5.9 TB/s (as the cube root of the sum of cubes: near the crossing both are felt); and
+// 3.2 plus 0.04 a split and the partials'
+// traffic for the merge kernel. Measured (us a layer; 28 query heads over 4 kv-heads of 128, one query): 16 streams of
+// 16585 keys 148.7 unsplit, 33.5 in 8, 28.5 in 12, 29.8 in 16; 160 streams of 4297 keys 61.6 unsplit
+// and 75.7 in two, which take a second round; 4 streams of 1225 keys 16.7 unsplit, 8.7 in ten.
+// Keys are split only within one round of 256 blocks (one per CU), so the largest split, which the
+// recommended workspace has room for, never falls as the keys grow.
+static int64_t ksplit_max_splits(int64_t units, int64_t tiles) {
+  return std::max<int64_t>(1, std::min<int64_t>(64, std::min<int64_t>(tiles / 2, 256 / units)));
+}
+static int64_t ksplit_splits(int64_t units, int64_t tiles, int64_t per_split, double kv_bytes, int64_t fit) {
+  int64_t best = 1;
+  double best_us = 0.0;
+  const int64_t smax = ksplit_max_splits(units, tiles);
+  for (int64_t sp = 1; sp <= smax && (sp == 1 || sp <= fit); ++sp) {
+    const double x = 1.12 * (double)cdiv64(cdiv64(tiles, sp), ksplit::NWAVE), y = kv_bytes / 5.9e6;
+    double us = std::cbrt(x * x * x + y * y * y);
+    if (sp > 1) us += 3.2 + (double)sp * (0.04 + 2.0 * (double)per_split / 4.0e6);
+    if (sp == 1 || us < best_us) {
+      best = sp;
+      best_us = us;
+    }
+  }
+  return best;
+}
 
 AttnPlan plan_attention(int B, int Hq, int Hkv, int hd, int Nv, int Nq, int Nkt, int q_pos0,
                         int dtype, size_t ws_bytes) {
@@ -1359,7 +1450,13 @@ AttnPlan plan_attention(int B, int Hq, int Hkv, int hd, int Nv, int Nq, int Nkt,
   const int64_t per_split = rows_total * (int64_t)(hd + 2) * 4;
   const int max_keys = Nv + q_pos0 + Nq;  // keys seen by the last query
   const int n_bg = B * Hkv;
-  p.decode = (Nq == 1 && G <= 8);
+  // One query per sequence. A GQA group in bf16 with hd 128 goes to the key-split kernel: the decode
+  // kernel's VALU work grows with G while its bytes do not (28 query heads over 4 kv-heads, B 4 x
+  // 16585 keys: 110.8 -> 29 us a layer; G = 2, B 16 x 4397 keys: 57.5 -> 53.6 us). With one head per
+  // kv-head the decode kernel, which needs no LDS, holds more loads in flight (B 16 x 877 keys: 40.1
+  // against 44.0 us).
+  p.dec = Nq == 1 && G >= 2 && G <= 8 && dtype == 1 && hd == 128;
+  p.decode = Nq == 1 && G <= 8 && !p.dec;
   p.stream = !p.decode && dtype == 1 && hd == 128;
   int64_t units, tiles;
   int64_t min_blocks = 512;
@@ -1416,6 +1513,8 @@ AttnPlan plan_attention(int B, int Hq, int Hkv, int hd, int Nv, int Nq, int Nkt,
       }
     }
     want = best;
+  } else if (p.ksplit) {
+    want = ksplit_splits(units, tiles, per_split, (double)n_bg * max_keys * hd * 4, fit);
   } else if (want > 1 && per_split > 0) {
     want = std::min<int64_t>(want, fit);
     if (want < 2) want = 1;
@@ -1425,6 +1524,8 @@ AttnPlan plan_attention(int B, int Hq, int Hkv, int hd, int Nv, int Nq, int Nkt,
   p.keys_per_split = (int)(tiles_per_split * 64);
   p.splits = (int)cdiv64(tiles, tiles_per_split);  // drop empty trailing splits
   p.ws_needed = p.splits > 1 ? (size_t)(p.splits * per_split) : 0;
+  const int64_t room = p.ksplit ? ksplit_max_splits(units, tiles) : p.splits;
+  p.ws_room = room > 1 ? (size_t)(room * per_split) : 0;
   return p;
 }
 
@@ -1432,7 +1533,7 @@ size_t attention_workspace(int B, int Hq, int Hkv, int hd, int Nv, int Nq, int N
   // The largest need over both dtypes and every valid q_pos0 (more keys never mean fewer splits).
   const AttnPlan p0 = plan_attention(B, Hq, Hkv, hd, Nv, Nq, Nkt, Nkt - Nq, 0, (size_t)-1);
   const AttnPlan p1 = plan_attention(B, Hq, Hkv, hd, Nv, Nq, Nkt, Nkt - Nq, 1, (size_t)-1);
-  return std::max(p0.ws_needed, p1.ws_needed);
+  return std::max(p0.ws_room, p1.ws_room);
 }
 
 template <typename T, int HD>
@@ -1444,6 +1545,8 @@ static hipError_t attn_launch_t(const AttnArgs& a, const AttnPlan& p, hipStream_
     const int G = a.Hq / a.Hkv;
     if (G == 1)
       k_attn_decode<T, HD, 1><<<grid, dim3(256), 0, s>>>(a);
+    else if constexpr (sizeof(T) == 2 && HD == 128)
+      return hipErrorInvalidValue;  // the planner takes the key-split kernel for these groups
     else if (G == 2)
       k_attn_decode<T, HD, 2><<<grid, dim3(256), 0, s>>>(a);
     else if (G <= 4)
@@ -1467,12 +1570,17 @@ static hipError_t attn_launch_t(const AttnArgs& a, const AttnPlan& p, hipStream_
       dim3 grid(a.B * a.Hkv * p.row_blocks, p.splits);
       if (p.ksplit) {
         static bool once_k = [] {
-          (void)hipFuncSetAttribute((const void*)k_attn_ksplit,
+          (void)hipFuncSetAttribute((const void*)k_attn_ksplit<false>,
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, ksplit::LDS_BYTES);
+          (void)hipFuncSetAttribute((const void*)k_attn_ksplit<true>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, ksplit::LDS_BYTES);
           return true;
         }();
         (void)once_k;
-        k_attn_ksplit<<<grid, dim3(ksplit::NWAVE * 64), ksplit::LDS_BYTES, s>>>(a, p.row_blocks);
+        if (p.dec)
+          k_attn_ksplit<true><<<grid, dim3(ksplit::NWAVE * 64), ksplit::LDS_BYTES, s>>>(a, p.row_blocks);
+        else
+          k_attn_ksplit<false><<<grid, dim3(ksplit::NWAVE * 64), ksplit::LDS_BYTES, s>>>(a, p.row_blocks);
       } else if (p.pp) {
         if (p.row_blocks == 1)  // each tile has one reader
           k_attn_pp<CPOL_NT><<<grid, dim3(pp::NWAVE * 64), pp::LDS_BYTES, s>>>(a, p.row_blocks);
@@ -1502,8 +1610,18 @@ static hipError_t attn_launch_t(const AttnArgs& a, const AttnPlan& p, hipStream_
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.splits == 1) return e;
   const int64_t rows = (int64_t)a.B * a.Nq * a.Hq;
-  const int64_t threads = rows * (HD / 4);
-  k_attn_combine<T, HD><<<dim3((unsigned)cdiv64(threads, 256)), dim3(256), 0, s>>>((const float*)a.Opart, (const float*)a.MLpart, (T*)a.O, rows, p.splits);
+  constexpr int kSlots = 256 / (HD / 4);
+  // Groups per row: more of them shorten each thread's chain of loads where few rows leave the chip
+  // idle (112 rows, 33 splits: 18.4 us a layer with one group, 14.6 with eight), and only add LDS
+  // traffic where the rows fill it (4096 rows, 2 splits: 14.2 with one, 16.2 with eight).
+  int sg = 1;
+  while (sg < 8 && sg * 4 <= p.splits && rows * sg * 2 <= 2048) sg *= 2;
+  const dim3 gc((unsigned)cdiv64(rows * sg, kSlots));
+  const float *po = a.Opart, *pm = a.MLpart;
+  if (sg == 8) k_attn_combine<T, HD, 8><<<gc, dim3(256), 0, s>>>(po, pm, (T*)a.O, rows, p.splits);
+  else if (sg == 4) k_attn_combine<T, HD, 4><<<gc, dim3(256), 0, s>>>(po, pm, (T*)a.O, rows, p.splits);
+  else if (sg == 2) k_attn_combine<T, HD, 2><<<gc, dim3(256), 0, s>>>(po, pm, (T*)a.O, rows, p.splits);
+  else k_attn_combine<T, HD, 1><<<gc, dim3(256), 0, s>>>(po, pm, (T*)a.O, rows, p.splits);
   return hipGetLastError();
 }
 

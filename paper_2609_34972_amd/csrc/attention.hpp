@@ -28,8 +28,9 @@ struct AttnArgs {
 };
 
 struct AttnPlan {
-  bool decode;         // one query per sequence: the bandwidth-bound kernel
+  bool decode;         // one query per sequence: the bandwidth-bound VALU kernel
   bool stream;         // bf16 hd-128 prefill: direct-to-LDS streaming kernel
+  bool dec;            // (ksplit) one query per sequence of a GQA group: P in two bf16 parts
   bool ksplit;         // (stream) few rows per kv-head: four waves split the keys of 32 rows
   bool pp;             // (stream) over 96 rows per kv-head: the eight-wave ping-pong kernel
   int tiles_per_split;  // (stream) key tiles per split: 32 keys each if ksplit, else 64
@@ -38,6 +39,7 @@ struct AttnPlan {
   int splits;          // key splits merged by a log-sum-exp combine
   int keys_per_split;  // decode and the generic prefill: a multiple of their 64-key tile
   size_t ws_needed;    // bytes of partials for this plan
+  size_t ws_room;      // bytes that hold the plan of this shape for any smaller q_pos0 too
 };
 
 AttnPlan plan_attention(int B, int Hq, int Hkv, int hd, int Nv, int Nq, int Nkt, int q_pos0,
