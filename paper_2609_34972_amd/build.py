@@ -17,7 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdeltavision.so")
 INFO = os.path.join(HERE, "build_info.json")
-SOURCES = ["api.cpp", "build_kernels.hip", "attention.hip", "recurrent.hip", "delta_rule.hip",
+SOURCES = ["api.cpp", "build_kernels.hip", "attention.hip", "recurrent.hip", "delta_rule.hip", "delta_chunk.hip",
            "probe.hip", "fused_kv.hip"]
 ARCH = "gfx950"
 

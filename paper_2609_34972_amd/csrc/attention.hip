@@ -316,8 +316,6 @@ __device__ __forceinline__ int key_k(int row) { return row & 15; }
 __device__ __forceinline__ int key_v(int row) { return (row & 3) << 2; }
 }  // namespace stream
 
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-
 // Transposed LDS reads of V (ds_read_b64_tr_b16) issued as inline assembly. The compiler's
 // wait-count pass cannot tell an LDS read from the direct-to-LDS loads still in flight into the
 // other stages (one dynamic LDS object), so before every such read it can see it drains all of
@@ -332,9 +330,6 @@ __device__ __forceinline__ s16x4 lds_read_tr16(uint32_t base) {
   s16x4 r;
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(base), "n"(OFF));
   return r;
-}
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
 // V^T fragments of one 16-key step (keys KEY0 .. KEY0 + 15 of the stage's tile) for the four
 // 32-column blocks: col[cb] is the lane's address of key row vrow (< 8) of column block cb

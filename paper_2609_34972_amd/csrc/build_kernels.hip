@@ -496,9 +496,6 @@ __device__ __forceinline__ u32x2 lds_read_b64(uint32_t addr) {
 __device__ __forceinline__ void lds_write_b64(uint32_t addr, u32x2 v) {
   asm volatile("ds_write_b64 %0, %1" ::"v"(addr), "v"(v) : "memory");
 }
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
-}
 // Wait for the LDS reads in flight and tie their results to this point.
 template <class V, int N>
 __device__ __forceinline__ void lds_wait(V (&v)[N]) {

@@ -16,8 +16,8 @@
 // S = gamma_C S + Kt U. The rule acts on every state column independently: each wave keeps 32
 // columns of the fp32 state, all dk rows, in MFMA accumulators, and since those accumulators
 // (and those of U) are already the B operands of the next product in a permuted k order, a
-// wave's chain needs no exchange with other waves; the block only shares the chunk record,
-// copied into LDS one chunk ahead. Products read the state rounded to the call dtype; the
+// wave's chain needs no exchange with other waves; the block only shares the chunk record in LDS.
+// These are the fp32 kernels; bf16 calls take those of delta_chunk.hip. Products read the state rounded to the call dtype; the
 // state itself stays fp32.
 //
 // Long sequences use a two-level scan. The chunk step is affine in S, so a run of chunks maps
@@ -76,24 +76,15 @@ __device__ __forceinline__ int frag_off(int row, int pos) {
 template <typename T, int INNER>
 __device__ __forceinline__ typename Frag8<T>::type frag_get(const T* m, int row, int g) {
   typedef typename Frag8<T>::type F;
-  if constexpr (sizeof(T) == 2) {
-    return *(const F*)(m + frag_off<T, INNER>(row, 8 * g));
-  } else {
-    const f32x4 lo = *(const f32x4*)(m + frag_off<T, INNER>(row, 8 * g));
-    const f32x4 hi = *(const f32x4*)(m + frag_off<T, INNER>(row, 8 * g + 4));
-    return F{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-  }
+  const f32x4 lo = *(const f32x4*)(m + frag_off<T, INNER>(row, 8 * g));
+  const f32x4 hi = *(const f32x4*)(m + frag_off<T, INNER>(row, 8 * g + 4));
+  return F{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 }
 
 template <typename T, int INNER>
 __device__ __forceinline__ void frag_put(T* m, int row, int g, typename Frag8<T>::type x) {
-  typedef typename Frag8<T>::type F;
-  if constexpr (sizeof(T) == 2) {
-    *(F*)(m + frag_off<T, INNER>(row, 8 * g)) = x;
-  } else {
-    *(f32x4*)(m + frag_off<T, INNER>(row, 8 * g)) = f32x4{x[0], x[1], x[2], x[3]};
-    *(f32x4*)(m + frag_off<T, INNER>(row, 8 * g + 4)) = f32x4{x[4], x[5], x[6], x[7]};
-  }
+  *(f32x4*)(m + frag_off<T, INNER>(row, 8 * g)) = f32x4{x[0], x[1], x[2], x[3]};
+  *(f32x4*)(m + frag_off<T, INNER>(row, 8 * g + 4)) = f32x4{x[4], x[5], x[6], x[7]};
 }
 
 // Items 8 q .. 8 q + 7 of an accumulator tile, rounded to T: a B fragment in fragment order.
@@ -126,17 +117,12 @@ __device__ __forceinline__ int vk_off(int n, int s) {
 template <typename T>
 __device__ __forceinline__ typename Frag8<T>::type vk_frag(const T* m, int n, int s0) {
   typedef typename Frag8<T>::type F;
-  if constexpr (sizeof(T) == 2) {
-    return *(const F*)(m + vk_off<T>(n, s0));
-  } else {
-    const f32x4 lo = *(const f32x4*)(m + vk_off<T>(n, s0));
-    const f32x4 hi = *(const f32x4*)(m + vk_off<T>(n, s0 + 4));
-    return F{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-  }
+  const f32x4 lo = *(const f32x4*)(m + vk_off<T>(n, s0));
+  const f32x4 hi = *(const f32x4*)(m + vk_off<T>(n, s0 + 4));
+  return F{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 }
 
-// LDS layout of k_gdr_prep (byte offsets). M holds A and is turned into T = (I + A)^-1 in place;
-// the bf16 block stays under 53 KiB so that three share a CU.
+// LDS layout of k_gdr_prep (byte offsets). M holds A and is turned into T = (I + A)^-1 in place.
 template <typename T, int DK, int DV>
 struct GdrLds {
   static constexpr int C = gdr::C;
@@ -402,19 +388,14 @@ __device__ __forceinline__ int phi_off(int i, int j) {
   return i * DK + (((j >> 2) ^ (i & 15)) << 2) + (j & 3);
 }
 
-// LDS of k_gdr_chain: the chunk records in NS buffers (bf16: three, so that two records are in
-// flight while one is used; fp32: one). Per wave, a record copy is INS_PSI (with Uv) or INS_PHI
-// (without) 1 KiB instructions.
+// LDS of k_gdr_chain: one chunk record.
 template <typename T, int DK, int DV>
 struct ChainLds {
   typedef GdrRec<T, DK, DV> R;
-  static constexpr int NS = sizeof(T) == 2 ? 3 : 1;
-  static constexpr size_t bytes = (size_t)NS * R::ELEMS * sizeof(T);
-  static constexpr int INS_PSI = R::ELEMS * (int)sizeof(T) / 1024 / (gdr::NT / 64);
-  static constexpr int INS_PHI = R::UV * (int)sizeof(T) / 1024 / (gdr::NT / 64);
+  static constexpr size_t bytes = (size_t)R::ELEMS * sizeof(T);
   static_assert(R::ELEMS * sizeof(T) % (1024 * (gdr::NT / 64)) == 0 && R::UV * sizeof(T) % (1024 * (gdr::NT / 64)) == 0,
                 "every wave copies the same number of KiB");
-  static_assert(bytes <= 160 * 1024 && INS_PSI < 64, "fits LDS and the vmcnt counter");
+  static_assert(bytes <= 160 * 1024, "fits LDS");
 };
 
 // Copies one chunk record (a multiple of 1 KiB) into LDS, 1 KiB per wave instruction, waves
@@ -436,7 +417,6 @@ template <typename T, int DK, int DV>
 __global__ __launch_bounds__(gdr::NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gdr_chain(float* __restrict__ S, const float* __restrict__ gcs, int Hv, int N, GdrWs ws) {
   using namespace gdr;
   typedef GdrRec<T, DK, DV> R;
-  typedef ChainLds<T, DK, DV> L;
   constexpr int NKT = DK / 32, XPHI = gdr_xblocks(DK);
   extern __shared__ __align__(16) unsigned char smem[];
   const int P = ws.P;
@@ -475,30 +455,15 @@ __global__ __launch_bounds__(gdr::NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
     }
   }
 
-  auto issue = [&](int c, int stage) {
-    gdr_copy_record(ws.rec<T>(seq * NC + c), copy_bytes, smem + (size_t)stage * R::ELEMS * sizeof(T), wave, nins);
-  };
+  auto issue = [&](int c) { gdr_copy_record(ws.rec<T>(seq * NC + c), copy_bytes, smem, wave, nins); };
 
-  issue(c_begin, 0);
-  if (L::NS == 3 && c_begin + 1 < c_end) issue(c_begin + 1, 1);
-  int stage = 0;
+  issue(c_begin);
   for (int c = c_begin; c < c_end; ++c) {
     const float gc = gcs[seq * NC + c];
-    // This wave's copies of chunk c have landed (those of chunk c + 1, issued after them, may
-    // still be in flight); the barrier makes that true of every wave and ends every wave's reads
-    // of the buffer that chunk c + 2 goes to.
-    if (L::NS == 3 && c + 1 < c_end) {
-      if (uses_uv)
-        pipe_sync<waitcnt_imm(L::INS_PSI, 0)>();
-      else
-        pipe_sync<waitcnt_imm(L::INS_PHI, 0)>();
-    } else {
-      pipe_sync<waitcnt_imm(0, 0)>();
-    }
-    if (L::NS == 3 && c + 2 < c_end) issue(c + 2, stage == 0 ? 2 : stage - 1);
+    pipe_sync<waitcnt_imm(0, 0)>();  // chunk c has landed for every wave
     if (active) {
       typedef typename Frag8<T>::type F;
-      const T* Wn = (const T*)(smem + (size_t)stage * R::ELEMS * sizeof(T));
+      const T* Wn = (const T*)smem;
       const T* Kt = Wn + R::KT;
       const T* UvT = Wn + R::UV;
       // Every fragment of the step is read up front (one block per CU leaves the registers
@@ -557,23 +522,11 @@ __global__ __launch_bounds__(gdr::NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
         for (int q = 0; q < 2; ++q)
 #pragma unroll
           for (int kt = 0; kt < NKT; ++kt) mfma_k16(st[kt], kf[kt][tt][q], ub[tt][q]);
-      // Schedule: the W and Uv reads first, then the U products with the Kt reads between them
-      // (they land while the products run), then the state products.
-      if constexpr (sizeof(T) == 2) {
-        __builtin_amdgcn_sched_group_barrier(0x100, 4 * NKT + 4, 0);
-#pragma unroll
-        for (int i = 0; i < 4 * NKT; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, 4 * NKT, 0);
-      }
     }
-    if (L::NS == 1 && c + 1 < c_end) {
+    if (c + 1 < c_end) {
       __syncthreads();
-      issue(c + 1, 0);
+      issue(c + 1);
     }
-    stage = L::NS == 3 ? (stage == 2 ? 0 : stage + 1) : 0;
   }
   if (!active) return;
   if (phi) {
@@ -715,26 +668,31 @@ static hipError_t gdr_launch(const void* k, const void* v, const float* alpha, c
   return hipGetLastError();
 }
 
-// Segments of the two-level scan, from a model of k_gdr_chain fitted on MI355X: one block per
-// CU, a chunk step bounded by the record stream of one CU (about 35 GB/s, 1.4 us for a 48 KiB
-// record) or by its MFMA chain (about 0.6 us), the records of all offset blocks together by HBM
-// (about 4.4 TB/s), and about 3 us per segment in k_gdr_merge. The transition-matrix blocks
-// read the same records as the offset blocks of their segment, at about the same time; counting
-// their bytes in the HBM term as well made the model choose fewer segments than the measured
-// optimum (4 for 256 chunks x 32 heads). P = 1 runs the whole sequence in order. The grid
-// dimension B * P stays within 65535.
-static void gdr_segments(int NC, int B, int Hv, int dk, int dv, int esize, int& P, int& cps) {
-  const double cus = 256.0, merge_us = 3.0, cu_bytes_per_us = 35.0e3, hbm_bytes_per_us = 4.4e6;
+// Segments of the two-level scan, from a model of the scan kernels' time on MI355X in us. P = 1 runs the
+// whole sequence in order. The grid dimension B * P stays within 65535.
+//   bf16 (k_gdr_scan, one block per CU): 1.4 a chunk in order; 2.0 to 2.5 (more as the chip fills) with the
+//   transition matrix beside it; k_gdr_join 4 plus 1.6 a segment. Video of 256 chunks x 32 heads, write
+//   in all: 388 in order, 186 in 4 segments, 139 in 8, 169 in 12; 63 chunks x 64 sequences: 115 in order,
+//   82 in 4 segments, 95 in 8; 9 chunks x 128: 32 in order, 37 in 2.
+//   fp32 (k_gdr_chain, one block per CU): a chunk step bounded by the record stream of one CU (about 35
+//   GB/s), the records of all offset blocks together by HBM (about 4.4 TB/s), about 3 per segment in
+//   k_gdr_merge. The transition-matrix blocks read the same records as the offset blocks of their
+//   segment, at about the same time, so their bytes are not counted again.
+static void gdr_segments(int NC, int B, int Hv, int dk, int dv, int dtype, int& P, int& cps) {
+  const double cus = 256.0;
   const double seqs = (double)B * Hv;
-  const double rec = 64.0 * (2 * dk + dv) * esize;
-  const double step_us = std::max(0.6, rec / cu_bytes_per_us);
+  const double rec = 64.0 * (2 * dk + dv) * 4;
   const int xk = gdr_xblocks(dk), xv = gdr_xblocks(dv);
+  const double size = 0.5 + 0.5 * (double)(dk * dv) / 16384.0;  // 64-wide heads: shorter products
   auto cost = [&](int p, int c) {
+    if (dtype == 1) {
+      const double rounds = std::ceil(seqs * p / cus);
+      if (p == 1) return rounds * c * 1.4 * size;
+      return rounds * c * (2.0 + 0.5 * std::min(1.0, seqs * p / cus)) * size + 4.0 + 1.6 * (p - 1);
+    }
     const double blocks = seqs * (p > 1 ? (double)p * (xk + xv) - xk : xv);
-    const double rounds = std::ceil(blocks / cus);
-    const double bytes = seqs * NC * rec * xv;
-    const double t = std::max(rounds * c * step_us, bytes / hbm_bytes_per_us);
-    return t + (p > 1 ? (p - 1) * merge_us * std::ceil(seqs * xv / cus) : 0.0);
+    const double t = std::max(std::ceil(blocks / cus) * c * std::max(0.6, rec / 35.0e3), seqs * NC * rec * xv / 4.4e6);
+    return t + (p > 1 ? (p - 1) * 3.0 * std::ceil(seqs * xv / cus) : 0.0);
   };
   P = 1;
   cps = NC;
@@ -758,8 +716,8 @@ GdrWs gdr_layout(void* base, int B, int Hv, int N, int dk, int dv, int dtype) {
   const int64_t chunks = (int64_t)B * Hv * NC;
   auto al = [](size_t x) { return (x + 255) / 256 * 256; };
   GdrWs w{};
-  gdr_segments(NC, B, Hv, dk, dv, (int)e, w.P, w.cps);
-  w.rec_elems = gdr::C * (2 * dk + dv);
+  gdr_segments(NC, B, Hv, dk, dv, dtype, w.P, w.cps);
+  w.rec_elems = dtype == 1 ? kGdrRecBytes / 2 : gdr::C * (2 * dk + dv);
   char* p = (char*)base;
   size_t o = 0;
   w.rec_ = p ? p + o : nullptr;
@@ -767,7 +725,7 @@ GdrWs gdr_layout(void* base, int B, int Hv, int N, int dk, int dv, int dtype) {
   w.gc = p ? (float*)(p + o) : nullptr;
   o += al((size_t)chunks * 4);
   const size_t segs = w.P > 1 ? (size_t)B * Hv * w.P : 0;
-  w.phi = p ? (float*)(p + o) : nullptr;  o += al(segs * dk * dk * 4);
+  w.phi = p ? (float*)(p + o) : nullptr;  o += al(segs * dk * dk * e);
   w.psi = p ? (float*)(p + o) : nullptr;  o += al(segs * dk * dv * 4);
   w.bytes = o;
   return w;
@@ -776,12 +734,7 @@ GdrWs gdr_layout(void* base, int B, int Hv, int N, int dk, int dv, int dtype) {
 hipError_t launch_delta_rule(const void* k, const void* v, const float* alpha, const float* beta,
                              float* S, int B, int Hk, int Hv, int N, int dk, int dv, int dtype,
                              GdrWs ws, hipStream_t s, const LaunchEvents& ev) {
-  if (dtype == 1) {
-    if (dk == 128 && dv == 128) return gdr_launch<bf16, 128, 128>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);
-    if (dk == 128 && dv == 64) return gdr_launch<bf16, 128, 64>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);
-    if (dk == 64 && dv == 128) return gdr_launch<bf16, 64, 128>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);
-    return gdr_launch<bf16, 64, 64>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);
-  }
+  if (dtype == 1) return launch_delta_chunk(k, v, alpha, beta, S, B, Hk, Hv, N, dk, dv, ws, s, ev);
   if (dk == 128 && dv == 128) return gdr_launch<float, 128, 128>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);
   if (dk == 128 && dv == 64) return gdr_launch<float, 128, 64>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);
   if (dk == 64 && dv == 128) return gdr_launch<float, 64, 128>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);

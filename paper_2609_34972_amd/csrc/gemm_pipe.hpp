@@ -47,6 +47,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, 
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, nr, kRawBufferFlags);
 }
 
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// LDS byte address of a generic pointer into LDS, as inline assembly takes it.
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
 // One GEMM operand as row ranges of up to two buffers: rows [0, nsplit) come from r0, rows
 // [nsplit, ...) from r1 (row nsplit is r1's first row). Row pitch in bytes.
 struct BufOperand {
