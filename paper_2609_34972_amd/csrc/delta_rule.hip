@@ -697,7 +697,9 @@ static void gdr_segments(int NC, int B, int Hv, int dk, int dv, int dtype, int& 
   P = 1;
   cps = NC;
   double best = cost(1, NC);
-  const int pmax = std::min(64, std::min(NC / 2, 65535 / B));
+  int pmax = std::min(64, std::min(NC / 2, 65535 / B));
+  if (dtype == 1)  // the segments' maps fit beside the records in the workspace's fixed 64 (2 dk + dv) a chunk
+    pmax = std::min<int64_t>(pmax, (int64_t)NC * (128 * (2 * dk + dv) - kGdrRecBytes) / (2 * dk * dk + 4 * dk * dv));
   for (int p = 2; p <= pmax; ++p) {
     const int c = (NC + p - 1) / p;
     const int pp = (NC + c - 1) / c;
@@ -727,7 +729,8 @@ GdrWs gdr_layout(void* base, int B, int Hv, int N, int dk, int dv, int dtype) {
   const size_t segs = w.P > 1 ? (size_t)B * Hv * w.P : 0;
   w.phi = p ? (float*)(p + o) : nullptr;  o += al(segs * dk * dk * e);
   w.psi = p ? (float*)(p + o) : nullptr;  o += al(segs * dk * dv * 4);
-  w.bytes = o;
+  // The size that callers have always been told: full chunk records, whatever the bf16 kernels store.
+  w.bytes = std::max(o, al((size_t)chunks * 64 * (2 * dk + dv) * e) + al((size_t)chunks * 4));
   return w;
 }
 
