@@ -271,7 +271,7 @@ __device__ __forceinline__ void load4_bf16(const bf16* p, float (&x)[4]) {
   for (int e = 0; e < 4; ++e) x[e] = (float)v[e];
 }
 
-template <class C, int ACT>
+template <class C, int ACT, int NS>
 __global__ __launch_bounds__(C::NT) void k_down_act_p(const bf16* __restrict__ E,
                                                       const bf16* __restrict__ Dw,
                                                       bf16* __restrict__ Z, int T, int d, int L,
@@ -285,11 +285,11 @@ __global__ __launch_bounds__(C::NT) void k_down_act_p(const bf16* __restrict__ E
                buffer_rsrc(E, 0), 1 << 30, ldb};
   BufOperand B{buffer_rsrc(Dw + (int64_t)n0 * d, (int64_t)(N - n0) * ldb),
                buffer_rsrc(Dw, 0), 1 << 30, ldb};
-  f32x4 acc[C::FM][C::FN];
-  pipe_mainloop<C>(A, B, d, (bf16*)smem, acc);
-
   const int lane = threadIdx.x & 63, wave = wave_index();
   const int wm = wave / C::WGN, wn = wave % C::WGN;
+  f32x4 acc[C::FM][C::FN];
+  pipe_mainloop<C, NS>(A, B, d, (bf16*)smem, acc, wm * C::WM < T - m0);
+
 #pragma unroll
   for (int a = 0; a < C::FM; ++a) {
     const int row = m0 + wm * C::WM + a * 16 + pipe_row(lane);
@@ -819,7 +819,8 @@ __global__ __launch_bounds__(KvP::NT) void k_kv_proj_p(const bf16* __restrict__ 
     part[i] = (rs_row < T && p < np) ? rs_src[(int64_t)p * T] : 0.f;
   }
   f32x4 acc[C::FM][C::FN];
-  pipe_mainloop<C>(A, B, d, (bf16*)smem, acc);
+  // A wave whose rows all lie past the end computes nothing (see pipe_mainloop).
+  pipe_mainloop<C>(A, B, d, (bf16*)smem, acc, wave_index() / C::WGN * C::WM < T - m0);
   {
     float sum = 0.f;
 #pragma unroll
@@ -1045,6 +1046,8 @@ static void allow_lds(K kernel, int bytes) {
 
 // ---------------------------------------------------------------- launchers
 
+static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+
 // Supertile shapes of the pipelined down and up projections (see supertile_order).
 struct TileOrder {
   int sh, sw;
@@ -1054,14 +1057,40 @@ static TileOrder up_order() { return TileOrder{8, 8}; }
 
 // Layers per block of the tiled up projection. A block reads its tile of E once for all its
 // layers and runs them through one pipeline, which saves E reads and block starts; fewer, longer
-// blocks balance worse over the CUs. Measured (ms, per step): Qwen2.5-VL video 2.27 with 4
+// blocks balance worse over the CUs. Of 1 to 8 layers the count is taken whose blocks, dealt in order
+// to the 512 slots (two per CU), end first, a block costing its layers plus 0.7 for its start.
+// Measured (us, 17 layers of d = 4096, r = 256, eight layers a block against this rule): 64 tokens
+// 40 -> 17, 256 45 -> 32, 576 58 -> 49. Full launches keep eight (ms): Qwen2.5-VL video 2.27 with 4
 // layers, 2.18 with 8, 2.28-2.40 with 14, 16 or 28; LLaVA-7B 0.31 with 4 or 8, 0.33 with 16.
 static int up_layers_per_block(int64_t tiles_per_layer, int nl) {
-  (void)tiles_per_layer;
-  return std::min(nl, 8);
+  const int64_t slots = 512;
+  int best = 1;
+  double best_end = 0.0;
+  for (int lpb = 1; lpb <= std::min(nl, 8); ++lpb) {
+    const int64_t whole = tiles_per_layer * (nl / lpb);
+    const int rest = nl % lpb;
+    const double c1 = lpb + 0.7, c2 = rest + 0.7;
+    // after the blocks of lpb layers: some slots are busy until hi, the others until lo
+    int64_t n_hi = whole % slots, n_lo = slots - n_hi, left = rest ? tiles_per_layer : 0;
+    double lo = (double)(whole / slots) * c1, hi = lo + c1;
+    double end = n_hi ? hi : lo;
+    while (left > 0) {  // the blocks of the remaining layers go to the slots that are free first
+      const int64_t n = std::min(left, n_lo);
+      lo += c2;
+      end = std::max(end, lo);
+      left -= n;
+      if (n_hi && hi < lo) {
+        std::swap(lo, hi);
+        std::swap(n_lo, n_hi);
+      }
+    }
+    if (lpb == 1 || end <= best_end) {
+      best = lpb;
+      best_end = end;
+    }
+  }
+  return best;
 }
-
-static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 template <typename T>
 static hipError_t down_launch(const void* E, const void* Dw, void* Z, int T_, int d, int L, int r,
@@ -1077,10 +1106,21 @@ static hipError_t down_launch(const void* E, const void* Dw, void* Z, int T_, in
   return hipGetLastError();
 }
 
+typedef void (*DownKernel)(const bf16*, const bf16*, bf16*, int, int, int, int, int, int);
+static hipError_t down_run(DownKernel kernel, int bm, int bn, int nt, int lds, const void* E, const void* Dw,
+                           void* Z, int T_, int d, int L, int r, hipStream_t s, const LaunchEvents& ev) {
+  const TileOrder ord = down_order();
+  record(ev.down[0], s);
+  kernel<<<dim3(cdiv((int64_t)L * r, bn), cdiv(T_, bm)), dim3(nt), lds, s>>>((const bf16*)E, (const bf16*)Dw, (bf16*)Z,
+                                                                            T_, d, L, r, ord.sh, ord.sw);
+  record(ev.down[1], s);
+  return hipGetLastError();
+}
+
 hipError_t launch_down_act(const void* E, const void* Dw, void* Z, int64_t T_, int d, int L,
                            int r, int act, int dtype, hipStream_t s, const LaunchEvents& ev) {
   if (dtype == 1) {
-    // Three tile shapes; each is priced as rounds of its block slots times the outputs a CU
+    // Otherwise three tile shapes; each is priced as rounds of its block slots times the outputs a CU
     // computes per round, and the cheapest wins, ties going to the larger tile (fewer operand
     // bytes per MFMA): 256 x 256 (one block per CU), 192 x 128 with eight waves and 128 x 128
     // with four (two blocks per CU each; two 192 x 128 blocks take all 160 KiB of LDS, and forcing
@@ -1088,50 +1128,38 @@ hipError_t launch_down_act(const void* E, const void* Dw, void* Z, int64_t T_, i
     // (0.180 -> 0.149 ms against the earlier 96 x 128 blocks, bit-identical), LLaVA-NeXT's 23040 x
     // 8192 15 rounds of 192 x 128 instead of 11.25 of 256 x 256 (1.47 -> 1.31-1.41 ms), and
     // Qwen2.5-VL video's 16384 x 14336 14 whole rounds of 256 x 256.
-    static bool once = [] {
-      allow_lds(k_down_act_p<KvP, 0>, KvP::LDS_BYTES);
-      allow_lds(k_down_act_p<KvP, 1>, KvP::LDS_BYTES);
-      allow_lds(k_down_act_p<DownP192, 0>, DownP192::LDS_BYTES);
-      allow_lds(k_down_act_p<DownP192, 1>, DownP192::LDS_BYTES);
-      return true;
-    }();
-    (void)once;
     const int64_t N = (int64_t)L * r;
+    const int64_t t128 = (int64_t)cdiv(N, DownP::BN) * cdiv(T_, DownP::BM);
     const int64_t c256 = (int64_t)cdiv(cdiv(N, KvP::BN) * cdiv(T_, KvP::BM), 256) * 256 * 256;
     const int64_t c192 =
         (int64_t)cdiv(cdiv(N, DownP192::BN) * cdiv(T_, DownP192::BM), 512) * 2 * 192 * 128;
-    const int64_t c128 = (int64_t)cdiv(cdiv(N, DownP::BN) * cdiv(T_, DownP::BM), 512) * 2 * 128 * 128;
-    const bool big = c256 <= c192 && c256 <= c128;
-    const bool rows192 = !big && c192 <= c128;
-    const TileOrder ord = down_order();
-    record(ev.down[0], s);
-    if (big) {
-      dim3 grid(cdiv(N, KvP::BN), cdiv(T_, KvP::BM));
-      if (act == 0)
-        k_down_act_p<KvP, 0><<<grid, dim3(KvP::NT), KvP::LDS_BYTES, s>>>((const bf16*)E, (const bf16*)Dw,
-                                                                         (bf16*)Z, (int)T_, d, L, r, ord.sh, ord.sw);
-      else
-        k_down_act_p<KvP, 1><<<grid, dim3(KvP::NT), KvP::LDS_BYTES, s>>>((const bf16*)E, (const bf16*)Dw,
-                                                                         (bf16*)Z, (int)T_, d, L, r, ord.sh, ord.sw);
-    } else if (rows192) {
-      dim3 grid(cdiv(N, DownP192::BN), cdiv(T_, DownP192::BM));
-      if (act == 0)
-        k_down_act_p<DownP192, 0><<<grid, dim3(DownP192::NT), DownP192::LDS_BYTES, s>>>(
-            (const bf16*)E, (const bf16*)Dw, (bf16*)Z, (int)T_, d, L, r, ord.sh, ord.sw);
-      else
-        k_down_act_p<DownP192, 1><<<grid, dim3(DownP192::NT), DownP192::LDS_BYTES, s>>>(
-            (const bf16*)E, (const bf16*)Dw, (bf16*)Z, (int)T_, d, L, r, ord.sh, ord.sw);
-    } else {
-      dim3 grid(cdiv(N, DownP::BN), cdiv(T_, DownP::BM));
-      if (act == 0)
-        k_down_act_p<DownP, 0><<<grid, dim3(DownP::NT), DownP::LDS_BYTES, s>>>(
-            (const bf16*)E, (const bf16*)Dw, (bf16*)Z, (int)T_, d, L, r, ord.sh, ord.sw);
-      else
-        k_down_act_p<DownP, 1><<<grid, dim3(DownP::NT), DownP::LDS_BYTES, s>>>(
-            (const bf16*)E, (const bf16*)Dw, (bf16*)Z, (int)T_, d, L, r, ord.sh, ord.sw);
-    }
-    record(ev.down[1], s);
-    return hipGetLastError();
+    const int64_t c128 = (int64_t)cdiv(t128, 512) * 2 * 128 * 128;
+    constexpr int kDeep = 4, kDeepLds = kDeep * DownP::STAGE * 2;
+    static bool once = [] {
+      allow_lds(k_down_act_p<KvP, 0, 2>, KvP::LDS_BYTES);
+      allow_lds(k_down_act_p<KvP, 1, 2>, KvP::LDS_BYTES);
+      allow_lds(k_down_act_p<DownP192, 0, 2>, DownP192::LDS_BYTES);
+      allow_lds(k_down_act_p<DownP192, 1, 2>, DownP192::LDS_BYTES);
+      allow_lds(k_down_act_p<DownP, 0, kDeep>, kDeepLds);
+      allow_lds(k_down_act_p<DownP, 1, kDeep>, kDeepLds);
+      return true;
+    }();
+    (void)once;
+    const bool silu = act == 0;
+    // At most one 128 x 128 tile per CU: four stages instead of two keep three K tiles in flight where
+    // no second block covers a load's latency (T 64 to 768 of 17 LLaVA layers: 60-66 -> 38-46 us). With more
+    // tiles than CUs the two-stage blocks, two to a CU, are faster.
+    if (t128 <= 256)
+      return down_run(silu ? k_down_act_p<DownP, 0, kDeep> : k_down_act_p<DownP, 1, kDeep>, DownP::BM, DownP::BN,
+                      DownP::NT, kDeepLds, E, Dw, Z, (int)T_, d, L, r, s, ev);
+    if (c256 <= c192 && c256 <= c128)
+      return down_run(silu ? k_down_act_p<KvP, 0, 2> : k_down_act_p<KvP, 1, 2>, KvP::BM, KvP::BN, KvP::NT,
+                      KvP::LDS_BYTES, E, Dw, Z, (int)T_, d, L, r, s, ev);
+    if (c192 <= c128)
+      return down_run(silu ? k_down_act_p<DownP192, 0, 2> : k_down_act_p<DownP192, 1, 2>, DownP192::BM, DownP192::BN,
+                      DownP192::NT, DownP192::LDS_BYTES, E, Dw, Z, (int)T_, d, L, r, s, ev);
+    return down_run(silu ? k_down_act_p<DownP, 0, 2> : k_down_act_p<DownP, 1, 2>, DownP::BM, DownP::BN, DownP::NT,
+                    DownP::LDS_BYTES, E, Dw, Z, (int)T_, d, L, r, s, ev);
   }
   return down_launch<float>(E, Dw, Z, (int)T_, d, L, r, act, s, ev);
 }

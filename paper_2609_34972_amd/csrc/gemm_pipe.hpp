@@ -126,7 +126,9 @@ __device__ __forceinline__ bool pipe_odd_block(int wave, int i) {
   return INS % 2 == 0 ? (i & 1) != 0 : ((wave * INS + i) & 1) != 0;
 }
 
-template <class C>
+// (NS, the caller's stage count, only tells the callers' instances apart: the host pass rejects the
+// resource type in an instance that two of them share.)
+template <class C, int NS>
 __device__ __forceinline__ void pipe_issue(const PipeLoads<C>& p, int kbytes, bf16* stage, int va0,
                                            int va1, int vb0, int vb1) {
   const int wave = wave_index();
@@ -229,10 +231,17 @@ __device__ __forceinline__ void pipe_step1_pattern() {
   }
 }
 
-// A: block-tile rows start at A's first row; B likewise. K must be a multiple of 64.
-template <class C>
+// A: block-tile rows start at A's first row; B likewise. K must be a multiple of 64. NS: stages in LDS.
+// Two are enough where two waves share a SIMD; where a launch leaves one small block on a CU, every K
+// tile waits out a load's latency, and four stages keep three tiles in flight (170 tiles of 128 x 128,
+// K = 4096: 62 us with two stages, 45 with four).
+// compute = false (wave-uniform): this wave's rows lie past the end. It loads its share and meets the
+// barriers, and leaves the matrix pipe to the other wave of its SIMD; its accumulators are zero.
+template <class C, int NS = 2>
 __device__ __forceinline__ void pipe_mainloop(const BufOperand& A, const BufOperand& B, int K,
-                                              bf16* lds, f32x4 (&acc)[C::FM][C::FN]) {
+                                              bf16* lds, f32x4 (&acc)[C::FM][C::FN],
+                                              bool compute = true) {
+  static_assert((NS - 1) * C::INS < 64, "vmcnt counts every load in flight");
 #pragma unroll
   for (int a = 0; a < C::FM; ++a)
 #pragma unroll
@@ -241,17 +250,28 @@ __device__ __forceinline__ void pipe_mainloop(const BufOperand& A, const BufOper
   const int vb0 = pipe_lane_offset(B.ld_bytes, 0), vb1 = pipe_lane_offset(B.ld_bytes, 1);
   const int nk = K / C::BK;
   const PipeLoads<C> pl = pipe_loads<C>(A, B);
-  pipe_issue<C>(pl, 0, lds, va0, va1, vb0, vb1);
-  if (nk > 1) {
-    pipe_issue<C>(pl, C::BK * 2, lds + C::STAGE, va0, va1, vb0, vb1);
-    pipe_sync<waitcnt_imm(C::INS, 0)>();  // tile 0 landed, tile 1 stays in flight
-  } else {
+  // Past the last tile the refill offset lies beyond the buffers' range (nothing is fetched; the
+  // stage, which is not read again, fills with zeros), so every wave counts the same loads.
+#pragma unroll
+  for (int t = 0; t < NS; ++t)
+    pipe_issue<C, NS>(pl, t < nk ? t * C::BK * 2 : kPipeOutOfRange, lds + t * C::STAGE, va0, va1, vb0, vb1);
+  pipe_sync<waitcnt_imm((NS - 1) * C::INS, 0)>();  // tile 0 landed, the others stay in flight
+  int st = 0;  // stage of tile kt
+  if (!compute) {
+    for (int kt = 0; kt < nk; ++kt) {
+      pipe_sync<waitcnt_imm((NS - 2) * C::INS, 0)>();
+      const int kb = kt + NS < nk ? (kt + NS) * C::BK * 2 : kPipeOutOfRange;
+      pipe_issue<C, NS>(pl, kb, lds + st * C::STAGE, va0, va1, vb0, vb1);
+      st = st + 1 == NS ? 0 : st + 1;
+    }
     pipe_sync<waitcnt_imm(0, 0)>();
+    return;
   }
   bf16x8 fa[2][C::FM], fb[2][C::FN];
   pipe_frags<C>(lds, 0, fa[0], fb[0]);
   for (int kt = 0; kt < nk; ++kt) {
-    bf16* s = lds + (kt & 1) * C::STAGE;
+    bf16* s = lds + st * C::STAGE;
+    st = st + 1 == NS ? 0 : st + 1;
     // K step 0: the step-1 fragments are read between its MFMAs (pipe_step0_pattern), so the
     // reads overlap the matrix pipe.
     pipe_frags<C>(s, 1, fa[1], fb[1]);
@@ -264,15 +284,13 @@ __device__ __forceinline__ void pipe_mainloop(const BufOperand& A, const BufOper
 #pragma unroll
       for (int b = 0; b < C::FN; ++b) asm volatile("" : "+v"(acc[a][b]));
     // K step 1: every wave holds its last fragments of stage s and tile kt+1 has landed:
-    // refill s with tile kt+2 and fetch tile kt+1's first fragments before this step's MFMAs.
-    pipe_sync<waitcnt_imm(0, 0)>();
+    // refill s with tile kt+NS and fetch tile kt+1's first fragments before this step's MFMAs.
+    pipe_sync<waitcnt_imm((NS - 2) * C::INS, 0)>();
     // Neither the refill nor the next fragment reads is conditional, so both interleave with
-    // this step's MFMAs: past the last tile the refill offset lies beyond the buffers' range
-    // (nothing is fetched; the stage, which is not read again, fills with zeros) and the
-    // fragments read from a stale stage go unused.
-    const int kb2 = kt + 2 < nk ? (kt + 2) * C::BK * 2 : kPipeOutOfRange;
-    pipe_issue<C>(pl, kb2, s, va0, va1, vb0, vb1);
-    pipe_frags<C>(lds + ((kt + 1) & 1) * C::STAGE, 0, fa[0], fb[0]);
+    // this step's MFMAs; the fragments read from a stale stage go unused.
+    const int kb = kt + NS < nk ? (kt + NS) * C::BK * 2 : kPipeOutOfRange;
+    pipe_issue<C, NS>(pl, kb, s, va0, va1, vb0, vb1);
+    pipe_frags<C>(lds + st * C::STAGE, 0, fa[0], fb[0]);
     pipe_mfmas<C>(acc, fa[1], fb[1]);
     pipe_step1_pattern<C>();
     __builtin_amdgcn_sched_barrier(0);  // keeps the two K steps' patterns in separate regions
