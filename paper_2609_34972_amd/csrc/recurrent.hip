@@ -148,18 +148,22 @@ __global__ __launch_bounds__(C::NT) void k_up_rec(const TIn* Min, float* Mst,
 
 // ------------------------------------------------------------------ pipelined bf16 kernels
 
-typedef PipeCfg<128, 128, 2, 2> RecP;
+typedef PipeCfg<128, 128, 2, 2> RecD;  // down projection, kRecStages stages: one block per CU
+constexpr int kRecStages = 4, kRecDownLds = kRecStages * RecD::STAGE * 2;
+// Up projection: 64-row tiles, three blocks per CU. With 128-row tiles, two per CU, LLaVA-7B's 576 blocks
+// took a second round for the last 64 (first layer 35.0 -> 29.9 us, the others 31.1 -> 30.3).
+typedef PipeCfg<64, 128, 2, 2> RecU;
 // Up-projection epilogue staging: the fp32 tile, rows padded by 4 floats.
-constexpr int kRecPitch = RecP::BN + 4;
-constexpr int kRecLds = RecP::BM * kRecPitch * 4 > RecP::LDS_BYTES ? RecP::BM * kRecPitch * 4
-                                                                   : RecP::LDS_BYTES;
+constexpr int kRecPitch = RecU::BN + 4;
+constexpr int kRecUpLds = RecU::BM * kRecPitch * 4 > RecU::LDS_BYTES ? RecU::BM * kRecPitch * 4
+                                                                     : RecU::LDS_BYTES;
 
 // partial[s][t][j] = sum over k in split s of X[t][k] * Dw_l[j][k]  (one 128x128 tile, one split)
-__global__ __launch_bounds__(RecP::NT) void k_down_partial_p(const bf16* __restrict__ X,
+__global__ __launch_bounds__(RecD::NT) void k_down_partial_p(const bf16* __restrict__ X,
                                                              const bf16* __restrict__ Dl,
                                                              float* __restrict__ part, int T, int d,
                                                              int r, int kchunk) {
-  typedef RecP C;
+  typedef RecD C;
   extern __shared__ __align__(16) unsigned char smem[];
   const int s = blockIdx.z;
   const int k0 = s * kchunk, klen = min(kchunk, d - k0);
@@ -172,9 +176,9 @@ __global__ __launch_bounds__(RecP::NT) void k_down_partial_p(const bf16* __restr
   BufOperand B{buffer_rsrc(Dl + (int64_t)n0 * d + k0, (int64_t)(r - n0) * ldb - (int64_t)k0 * 2),
                buffer_rsrc(Dl, 0), 1 << 30, ldb};
   f32x4 acc[C::FM][C::FN];
-  pipe_mainloop<C>(A, B, klen, (bf16*)smem, acc);
   const int lane = threadIdx.x & 63, wave = wave_index();
   const int wm = wave / C::WGN, wn = wave % C::WGN;
+  pipe_mainloop<C, kRecStages>(A, B, klen, (bf16*)smem, acc, wm * C::WM < T - m0);
   float* ps = part + (int64_t)s * T * r;
 #pragma unroll
   for (int a = 0; a < C::FM; ++a) {
@@ -202,20 +206,20 @@ __device__ __forceinline__ Prev8 load_prev8(const float* p) {
   return Prev8{*(const f32x4*)p, *(const f32x4*)(p + 4)};
 }
 
-// M_l = Min + Z_l U_l for a 128 x 128 tile. Min (E or the fp32 state, which it may alias) is
+// M_l = Min + Z_l U_l for a 64 x 128 tile. Min (E or the fp32 state, which it may alias) is
 // fetched before the main loop; the fp32 product goes through padded LDS so that 16 lanes cover
 // each 128-column row, and every output moves as whole pieces of a row: the fp32 state, its
 // bf16 copy (the next layer's down-projection operand), M * gamma and the row's sum of squares
 // over this column tile.
 template <typename TIn>
-__global__ __launch_bounds__(RecP::NT) void k_up_rec_p(const TIn* Min, float* Mst,
+__global__ __launch_bounds__(RecU::NT) void k_up_rec_p(const TIn* Min, float* Mst,
                                                        bf16* __restrict__ Mop,
                                                        const bf16* __restrict__ Z,
                                                        const bf16* __restrict__ Ul,
                                                        const bf16* __restrict__ gl,
                                                        bf16* __restrict__ Mg,
                                                        float* __restrict__ ssq, int T, int d, int r) {
-  typedef RecP C;
+  typedef RecU C;
   extern __shared__ __align__(16) unsigned char smem[];
   const int n0 = blockIdx.x * C::BN, m0 = blockIdx.y * C::BM;
   constexpr int kRows = C::BM / (C::NT / 16);
@@ -289,14 +293,18 @@ __global__ __launch_bounds__(RecP::NT) void k_up_rec_p(const TIn* Min, float* Ms
 
 static const int kMaxSplits = 16;
 
-// Split of the d-long reduction of the per-layer down projection: enough blocks to fill the
-// chip twice (at most kMaxSplits). Returns the chunk length; the split count is cdiv(d, chunk).
+// Split of the d-long reduction of the per-layer down projection: one block per CU where the splits
+// allow it (at most kMaxSplits). Returns the chunk length; the split count is cdiv(d, chunk). bf16: one
+// four-stage block per CU in half as many splits against two two-stage blocks (LLaVA-7B, us a layer):
+// down 16.5 -> 14.9, and k_reduce_act, which reads half the partials, 6.6 -> 5.1. The other engine's
+// blocks share a CU: enough of them to fill the chip twice.
 template <typename T>
 static int rec_kchunk(int T_, int d, int r) {
   typedef typename RecTiles<T>::C C;
   const int64_t blocks = (int64_t)rcdiv(r, C::BN) * rcdiv(T_, C::BM);
   const int ktiles = rcdiv(d, C::BK);
-  int s = (int)std::min<int64_t>(kMaxSplits, std::max<int64_t>(1, rcdiv(512, blocks)));
+  const int64_t want = std::is_same<T, bf16>::value && r % 64 == 0 ? 256 / blocks : rcdiv(512, blocks);
+  int s = (int)std::min<int64_t>(kMaxSplits, std::max<int64_t>(1, want));
   s = std::min(s, ktiles);
   return rcdiv(ktiles, s) * C::BK;
 }
@@ -336,23 +344,25 @@ static hipError_t rec_launch(const void* E, const void* Dw, const void* Uw, cons
   const int kchunk = w.kchunk;
   const bool pipelined = std::is_same<T, bf16>::value && r % 64 == 0;
   static bool once = [] {
+    (void)hipFuncSetAttribute((const void*)k_down_partial_p,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kRecDownLds);
     (void)hipFuncSetAttribute((const void*)k_up_rec_p<bf16>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, kRecLds);
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kRecUpLds);
     (void)hipFuncSetAttribute((const void*)k_up_rec_p<float>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, kRecLds);
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kRecUpLds);
     return true;
   }();
   (void)once;
   const int64_t nz = (int64_t)T_ * r;
   dim3 gd(rcdiv(r, C::BN), rcdiv(T_, C::BM), w.splits);
-  dim3 gu(rcdiv(d, C::BN), rcdiv(T_, C::BM));
+  dim3 gu(rcdiv(d, C::BN), rcdiv(T_, C::BM)), gp(rcdiv(d, RecU::BN), rcdiv(T_, RecU::BM));
   record(ev.down[0], s);
   for (int l = 0; l < L; ++l) {
     // Operand of this layer's down projection: E for the first layer, then the previous
     // memory (its rounded copy for bf16 runs, the fp32 state itself for fp32 runs).
     const T* X = l == 0 ? (const T*)E : (op ? (const T*)op : (const T*)state);
     if (pipelined)
-      k_down_partial_p<<<gd, dim3(RecP::NT), RecP::LDS_BYTES, s>>>(
+      k_down_partial_p<<<gd, dim3(RecD::NT), kRecDownLds, s>>>(
           (const bf16*)X, (const bf16*)Dw + (int64_t)l * r * d, part, T_, d, r, kchunk);
     else
       k_down_partial<C><<<gd, dim3(C::NT), C::LDS_BYTES, s>>>(X, (const T*)Dw + (int64_t)l * r * d,
@@ -366,11 +376,11 @@ static hipError_t rec_launch(const void* E, const void* Dw, const void* Uw, cons
     T* Mgl = Mg + (int64_t)l * T_ * d;
     float* ssql = ssq + (int64_t)l * w.np * T_;
     if (pipelined && l == 0)
-      k_up_rec_p<bf16><<<gu, dim3(RecP::NT), kRecLds, s>>>(
+      k_up_rec_p<bf16><<<gp, dim3(RecU::NT), kRecUpLds, s>>>(
           (const bf16*)E, state, (bf16*)op, (const bf16*)Z, (const bf16*)Ul, (const bf16*)gl,
           (bf16*)Mgl, ssql, T_, d, r);
     else if (pipelined)
-      k_up_rec_p<float><<<gu, dim3(RecP::NT), kRecLds, s>>>(
+      k_up_rec_p<float><<<gp, dim3(RecU::NT), kRecUpLds, s>>>(
           state, state, (bf16*)op, (const bf16*)Z, (const bf16*)Ul, (const bf16*)gl, (bf16*)Mgl,
           ssql, T_, d, r);
     else if (l == 0)
