@@ -283,6 +283,147 @@ __global__ __launch_bounds__(NW * 64) void k_attn_prefill(AttnArgs a) {
 }
 
 
+// ------------------------------------------------------------------ few rows (fp32)
+//
+// fp32 with up to 64 rows per kv-head: a block takes 16 rows and its waves take the 16-key tiles of
+// [visual; text] in turn, every fragment straight from global memory (float4 per lane), the next tile's
+// loads ahead of the products; the waves' partial (max, sum, O) meet in LDS at the end. The tile kernel
+// above gave 16 rows one wave of 32-row MFMAs that staged every 32 keys through LDS in turn: 12.3 us for 4
+// heads of 64, 16 rows and 80 keys.
+// 16x16x4 products with K step r of a 16-deep group taking k = 4 (lane / 16) + r: S^T = K Q^T leaves keys
+// 4 (lane / 16) + r of one query per lane, which is the B operand of O^T = V^T P^T as it stands, and V^T row
+// x of product c is channel 4 x + c, so that V too is read as float4.
+namespace f32rows {
+template <int HD> constexpr int waves() { return HD == 64 ? 8 : 4; }
+constexpr int MAXR = 64;
+}  // namespace f32rows
+
+template <int HD>
+__global__ __launch_bounds__(f32rows::waves<HD>() * 64) void k_attn_f32(AttnArgs a) {
+  constexpr int NW = f32rows::waves<HD>(), J = HD / 16, H2 = HD / 64, PITCH = HD + 4;
+  __shared__ __align__(16) float red_o[NW][16][PITCH];
+  __shared__ float red_m[NW][16], red_l[NW][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_index(), ln = lane & 15, kg = lane >> 4;
+  const int G = a.Hq / a.Hkv, R = a.Nq * G;
+  const int bg = blockIdx.y, b = bg / a.Hkv, g = bg - b * a.Hkv, split = blockIdx.z;
+  const int row0 = blockIdx.x * 16, my_row = min(row0 + ln, R - 1);
+  const int my_i = my_row / G, my_h = g * G + my_row - my_i * G;
+  const int i_max = (min(row0 + 16, R) - 1) / G;
+  const int k_begin = split * a.keys_per_split, k_end = min(a.Nv + a.q_pos0 + i_max + 1, k_begin + a.keys_per_split);
+  const int lim = a.Nv + a.q_pos0 + my_i;  // last key this lane's row may see
+  const float* Kvb = (const float*)a.Kv + (int64_t)bg * a.Nv * HD;
+  const float* Vvb = (const float*)a.Vv + (int64_t)bg * a.Nv * HD;
+  const float* Ktb = (const float*)a.Kt + (int64_t)bg * a.Nkt * HD;
+  const float* Vtb = (const float*)a.Vt + (int64_t)bg * a.Nkt * HD;
+
+  f32x4 q[J];
+  {
+    const float* qr = (const float*)a.Q + (((int64_t)b * a.Nq + my_i) * a.Hq + my_h) * HD + 4 * kg;
+#pragma unroll
+    for (int j = 0; j < J; ++j) q[j] = *(const f32x4*)(qr + 16 * j);
+  }
+  f32x4 kf[J], vf[H2][4];
+  auto load = [&](int t) {  // keys past the end: the last one again, masked below
+    const int kj = min(t + ln, k_end - 1);
+    const float* kp = (kj < a.Nv ? Kvb + (int64_t)kj * HD : Ktb + (int64_t)(kj - a.Nv) * HD) + 4 * kg;
+#pragma unroll
+    for (int j = 0; j < J; ++j) kf[j] = *(const f32x4*)(kp + 16 * j);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int vj = min(t + 4 * kg + r, k_end - 1);
+      const float* vp = (vj < a.Nv ? Vvb + (int64_t)vj * HD : Vtb + (int64_t)(vj - a.Nv) * HD) + 4 * ln;
+#pragma unroll
+      for (int h = 0; h < H2; ++h) vf[h][r] = *(const f32x4*)(vp + 64 * h);
+    }
+  };
+  f32x4 o[H2][4];
+#pragma unroll
+  for (int h = 0; h < H2; ++h)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) o[h][c] = f32x4{};
+  float m = NEG_BIG, l = 0.f;
+  int t = k_begin + wave * 16;
+  if (t < k_end) load(t);
+  for (; t < k_end; t += NW * 16) {
+    f32x4 s = {};
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][r], q[j][r], s, 0, 0, 0);
+    f32x4 vc[H2][4];
+#pragma unroll
+    for (int h = 0; h < H2; ++h)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) vc[h][r] = vf[h][r];
+    if (t + NW * 16 < k_end) load(t + NW * 16);
+    float mx = m;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int j = t + 4 * kg + r;
+      s[r] = j < k_end && j <= lim ? s[r] * a.scale_log2 : -INFINITY;
+      mx = fmaxf(mx, s[r]);
+    }
+    mx = fmaxf(mx, shfl_xor(mx, 16));
+    mx = fmaxf(mx, shfl_xor(mx, 32));
+    const float alpha = exp2f(m - mx);
+    m = mx;
+    float ps = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      s[r] = exp2f(s[r] - mx);
+      ps += s[r];
+    }
+    l = l * alpha + ps;
+#pragma unroll
+    for (int h = 0; h < H2; ++h)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        o[h][c] *= alpha;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[h][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[h][r][c], s[r], o[h][c], 0, 0, 0);
+      }
+  }
+  l += shfl_xor(l, 16);
+  l += shfl_xor(l, 32);
+#pragma unroll
+  for (int h = 0; h < H2; ++h)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *(f32x4*)&red_o[wave][ln][64 * h + 16 * kg + 4 * i] = f32x4{o[h][0][i], o[h][1][i], o[h][2][i], o[h][3][i]};
+  if (kg == 0) {
+    red_m[wave][ln] = m;
+    red_l[wave][ln] = l;
+  }
+  __syncthreads();
+  for (int idx = tid; idx < 16 * (HD / 4); idx += NW * 64) {
+    const int x = idx / (HD / 4), c = (idx % (HD / 4)) * 4, row = row0 + x;
+    if (row >= R) continue;
+    float mx = red_m[0][x];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) mx = fmaxf(mx, red_m[w][x]);
+    float lt = 0.f;
+    f32x4 acc = {};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float sc = exp2f(red_m[w][x] - mx);
+      lt += red_l[w][x] * sc;
+      acc += *(const f32x4*)&red_o[w][x][c] * sc;
+    }
+    const int i = row / G;
+    const int64_t orow = ((int64_t)b * a.Nq + i) * a.Hq + g * G + row - i * G;
+    if (a.splits == 1) {
+      *(f32x4*)((float*)a.O + orow * HD + c) = acc * (lt > 0.f ? 1.f / lt : 0.f);
+    } else {
+      const int64_t at = (int64_t)split * ((int64_t)a.B * a.Nq * a.Hq) + orow;
+      *(f32x4*)(a.Opart + at * HD + c) = acc;
+      if (c == 0) {
+        a.MLpart[at * 2] = mx;
+        a.MLpart[at * 2 + 1] = lt;
+      }
+    }
+  }
+}
+
 // ------------------------------------------------------------------ streaming prefill (bf16)
 
 namespace stream {
@@ -1421,6 +1562,9 @@ static inline int64_t cdiv64(int64_t x, int64_t y) { return (x + y - 1) / y; }
 static int64_t ksplit_max_splits(int64_t units, int64_t tiles) {
   return std::max<int64_t>(1, std::min<int64_t>(64, std::min<int64_t>(tiles / 2, 256 / units)));
 }
+static int64_t f32_max_splits(int64_t units, int64_t tiles, int nw) {
+  return std::max<int64_t>(1, std::min<int64_t>(64, std::min<int64_t>(cdiv64(tiles, nw), 256 / units)));
+}
 static int64_t ksplit_splits(int64_t units, int64_t tiles, int64_t per_split, double kv_bytes, int64_t fit) {
   int64_t best = 1;
   double best_us = 0.0;
@@ -1477,6 +1621,14 @@ AttnPlan plan_attention(int B, int Hq, int Hkv, int hd, int Nv, int Nq, int Nkt,
     }
     units = (int64_t)n_bg * p.row_blocks;
     min_blocks = 256;
+  } else if (dtype == 0 && (int64_t)Nq * G <= f32rows::MAXR) {
+    // Measured (us a layer, tile kernel against this one): 4 heads of 64, 16 rows, 80 keys 13.2 -> 5.8; 64
+    // rows, 364 keys 19.4 -> 9.7; 2 kv-heads of 128, 64 rows, 4016 keys 43.6 -> 13.4; 128 heads of 128, 64
+    // rows, 640 keys 51.3 -> 51.5. More rows share a K/V tile better in the tile kernel.
+    p.f32rows = true;
+    p.row_blocks = (int)cdiv64(Nq * G, 16);
+    units = (int64_t)n_bg * p.row_blocks;
+    tiles = cdiv64(max_keys, 16);
   } else {
     const int R = Nq * G;
     p.nw = R <= 32 ? 1 : (R <= 64 ? 2 : 4);
@@ -1492,7 +1644,22 @@ AttnPlan plan_attention(int B, int Hq, int Hkv, int hd, int Nv, int Nq, int Nkt,
   // Both streaming kernels hold one block per CU (LDS), so they run in rounds of 256 blocks.
   static_assert(stream::blocks_per_cu<2>() == 1, "two-wave streaming blocks: one per CU");
   const int64_t slots = 256;
-  if (p.stream && !p.ksplit && units < 256) {
+  if (p.f32rows) {
+    // Steps of a block (each of its waves takes a tile, about 0.6 us with 64-wide heads, 1.2 with 128),
+    // against about 3.5 us for the merge kernel; splits within one round of 256 blocks.
+    const int nw = hd == 64 ? f32rows::waves<64>() : f32rows::waves<128>();
+    const double step = hd == 64 ? 0.6 : 1.2;
+    const int64_t smax = f32_max_splits(units, tiles, nw);
+    double best = step * (double)cdiv64(tiles, nw);
+    want = 1;
+    for (int64_t sp = 2; sp <= smax && sp <= fit; ++sp) {
+      const double us = step * (double)cdiv64(cdiv64(tiles, sp), nw) + 3.5;
+      if (us < best) {
+        best = us;
+        want = sp;
+      }
+    }
+  } else if (p.stream && !p.ksplit && units < 256) {
     // Take the split count with the fewest tile steps over all rounds,
     // rounds(units * S) * ceil(tiles / S), preferring fewer splits on ties. Keys are split only
     // while some CU would have no block: with four-wave blocks two to a CU, LLaVA-NeXT's 256
@@ -1516,10 +1683,12 @@ AttnPlan plan_attention(int B, int Hq, int Hkv, int hd, int Nv, int Nq, int Nkt,
   }
   const int64_t tiles_per_split = cdiv64(tiles, want);
   p.tiles_per_split = (int)tiles_per_split;
-  p.keys_per_split = (int)(tiles_per_split * 64);
+  p.keys_per_split = (int)(tiles_per_split * (p.f32rows ? 16 : 64));
   p.splits = (int)cdiv64(tiles, tiles_per_split);  // drop empty trailing splits
   p.ws_needed = p.splits > 1 ? (size_t)(p.splits * per_split) : 0;
-  const int64_t room = p.ksplit ? ksplit_max_splits(units, tiles) : p.splits;
+  const int64_t room = p.ksplit ? ksplit_max_splits(units, tiles)
+                       : p.f32rows ? f32_max_splits(units, tiles, hd == 64 ? f32rows::waves<64>() : f32rows::waves<128>())
+                                   : p.splits;
   p.ws_room = room > 1 ? (size_t)(room * per_split) : 0;
   return p;
 }
@@ -1587,18 +1756,27 @@ static hipError_t attn_launch_t(const AttnArgs& a, const AttnPlan& p, hipStream_
     } else {
       return hipErrorInvalidValue;  // the planner only picks this kernel for bf16, hd 128
     }
+  } else if (p.f32rows) {
+    if constexpr (sizeof(T) == 4)
+      k_attn_f32<HD><<<dim3(p.row_blocks, a.B * a.Hkv, p.splits), dim3(f32rows::waves<HD>() * 64), 0, s>>>(a);
+    else
+      return hipErrorInvalidValue;  // the planner only picks this kernel for fp32
   } else {
     // bf16 hd-128 prefill always takes the streaming kernels, so no such instance is built.
     if constexpr (sizeof(T) == 2 && HD == 128) {
       return hipErrorInvalidValue;
     } else {
       dim3 grid(p.row_blocks, a.B * a.Hkv, p.splits);
-      if (p.nw == 1)
-        k_attn_prefill<T, HD, 1><<<grid, dim3(64), AttnCfg<T, HD, 1>::LDS_BYTES, s>>>(a);
-      else if (p.nw == 2)
-        k_attn_prefill<T, HD, 2><<<grid, dim3(128), AttnCfg<T, HD, 2>::LDS_BYTES, s>>>(a);
-      else
+      if constexpr (sizeof(T) == 2) {
+        if (p.nw == 1)
+          k_attn_prefill<T, HD, 1><<<grid, dim3(64), AttnCfg<T, HD, 1>::LDS_BYTES, s>>>(a);
+        else if (p.nw == 2)
+          k_attn_prefill<T, HD, 2><<<grid, dim3(128), AttnCfg<T, HD, 2>::LDS_BYTES, s>>>(a);
+        else
+          k_attn_prefill<T, HD, 4><<<grid, dim3(256), AttnCfg<T, HD, 4>::LDS_BYTES, s>>>(a);
+      } else {  // up to 64 rows take k_attn_f32
         k_attn_prefill<T, HD, 4><<<grid, dim3(256), AttnCfg<T, HD, 4>::LDS_BYTES, s>>>(a);
+      }
     }
   }
   record(ev.attn[1], s);

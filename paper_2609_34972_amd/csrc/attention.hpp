@@ -33,6 +33,7 @@ struct AttnPlan {
   bool dec;            // (ksplit) one query per sequence of a GQA group: P in two bf16 parts
   bool ksplit;         // (stream) few rows per kv-head: four waves split the keys of 32 rows
   bool pp;             // (stream) over 96 rows per kv-head: the eight-wave ping-pong kernel
+  bool f32rows;        // fp32, few rows per kv-head: 16-row blocks whose waves take the keys in turn
   int tiles_per_split;  // (stream) key tiles per split: 32 keys each if ksplit, else 64
   int nw;              // waves per block (prefill)
   int row_blocks;      // blocks along the packed (query, head) rows (prefill)

@@ -18,6 +18,7 @@
 #include "build_kernels.hpp"
 #include "gemm_pipe.hpp"
 #include "gemm_tile.hpp"
+#include "small_f32.hpp"
 
 #include <atomic>
 #include <utility>
@@ -1092,12 +1093,24 @@ static int up_layers_per_block(int64_t tiles_per_layer, int nl) {
   return best;
 }
 
+// Whether an fp32 call with this many 64 x 64 tiles takes the small-call kernels (small_f32.hip). Measured
+// (us, 64 x 64 tiles against the small kernels, a launch of about 4 us included): down projection 13.2 ->
+// 7.1 at 1 tile, 26.6 -> 17.2 at 60, 32.7 -> 20.7 at 64, 172 -> 273 at 288; K/V 14.0 -> 7.2 at 32 tiles,
+// 28.6 -> 14.0 at 48, 14.0 -> 12.8 and 126.9 -> 127.9 at 128, 32.6 -> 60.8 at 480; up projection 8.8 ->
+// 6.3 at 16, 9.9 -> 8.2 at 144, 17.1 -> 20.6 at 256 (r = 256), 15.6 -> 21.3 at 512.
+constexpr int64_t kSmallTiles = 96, kSmallUpTiles = 160;
+
 template <typename T>
 static hipError_t down_launch(const void* E, const void* Dw, void* Z, int T_, int d, int L, int r,
                               int act, hipStream_t s, const LaunchEvents& ev) {
   typedef typename BuildTiles<T>::Down C;
   dim3 grid(cdiv((int64_t)L * r, C::BN), cdiv(T_, C::BM));
   record(ev.down[0], s);
+  if ((int64_t)grid.x * grid.y <= kSmallTiles) {
+    const hipError_t e = launch_small_down((const float*)E, (const float*)Dw, (float*)Z, T_, d, L, r, act, s);
+    record(ev.down[1], s);
+    return e;
+  }
   if (act == 0)
     k_down_act<C, 0><<<grid, dim3(C::NT), C::LDS_BYTES, s>>>((const T*)E, (const T*)Dw, (T*)Z, T_, d, L, r);
   else
@@ -1208,6 +1221,12 @@ hipError_t launch_kv_only(const void* Mg, const float* ssq, const void* Wk, cons
   typedef typename BuildTiles<float>::KV CK;
   dim3 gk(cdiv(2 * Hkv * hd, CK::BN), cdiv(T_, CK::BM), nl);
   record(ev.kv[0], s);
+  if ((int64_t)gk.x * gk.y * gk.z <= kSmallTiles) {
+    const hipError_t e = launch_small_kv((const float*)Mg, ssq, (const float*)Wk, (const float*)Wv, (float*)Kv,
+                                         (float*)Vv, B_, Nv, d, Hkv, hd, l0, nl, np, eps, s);
+    record(ev.kv[1], s);
+    return e;
+  }
   k_kv_proj<CK><<<gk, dim3(CK::NT), CK::LDS_BYTES, s>>>((const float*)Mg, ssq, (const float*)Wk,
                                                          (const float*)Wv, (float*)Kv, (float*)Vv,
                                                          B_, Nv, d, Hkv, hd, l0, np, eps);
@@ -1305,18 +1324,31 @@ static hipError_t kv_launch(const void* E, const void* Z, const void* Uw, const 
   typedef typename BuildTiles<T>::Up CU;
   typedef typename BuildTiles<T>::KV CK;
   const int T_ = B_ * Nv;
+  constexpr bool f32 = std::is_same<T, float>::value;
+  static_assert(!f32 || CU::BN == 64, "the small kernels write one sum of squares per 64 columns");
   const int np = cdiv(d, CU::BN);
   dim3 gu(np, cdiv(T_, CU::BM), nl);
   if (first) record(ev.up[0], s);
-  k_up_norm<CU><<<gu, dim3(CU::NT), CU::LDS_BYTES, s>>>((const T*)E, (const T*)Z, (const T*)Uw, (const T*)gamma, (T*)Mg, ssq, T_, d, r, l0);
+  hipError_t e = hipSuccess;
+  if (f32 && (int64_t)gu.x * gu.y * gu.z <= kSmallUpTiles) {
+    e = launch_small_up((const float*)E, (const float*)Z, (const float*)Uw, (const float*)gamma, (float*)Mg, ssq, T_, d,
+                        r, l0, nl, s);
+  } else {
+    k_up_norm<CU><<<gu, dim3(CU::NT), CU::LDS_BYTES, s>>>((const T*)E, (const T*)Z, (const T*)Uw, (const T*)gamma, (T*)Mg, ssq, T_, d, r, l0);
+    e = hipGetLastError();
+  }
   if (last) record(ev.up[1], s);
-  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   dim3 gk(cdiv(2 * Hkv * hd, CK::BN), cdiv(T_, CK::BM), nl);
   if (first) record(ev.kv[0], s);
-  k_kv_proj<CK><<<gk, dim3(CK::NT), CK::LDS_BYTES, s>>>((const T*)Mg, ssq, (const T*)Wk, (const T*)Wv, (T*)Kv, (T*)Vv, B_, Nv, d, Hkv, hd, l0, np, eps);
+  if (f32 && (int64_t)gk.x * gk.y * gk.z <= kSmallTiles) {
+    e = launch_small_kv((const float*)Mg, ssq, (const float*)Wk, (const float*)Wv, (float*)Kv, (float*)Vv, B_, Nv, d,
+                        Hkv, hd, l0, nl, np, eps, s);
+  } else {
+    k_kv_proj<CK><<<gk, dim3(CK::NT), CK::LDS_BYTES, s>>>((const T*)Mg, ssq, (const T*)Wk, (const T*)Wv, (T*)Kv, (T*)Vv, B_, Nv, d, Hkv, hd, l0, np, eps);
+    e = hipGetLastError();
+  }
   if (last) record(ev.kv[1], s);
-  e = hipGetLastError();
   if (e != hipSuccess || !epi || !epi->any()) return e;
   return epi_post_launch<T>(Kv, Vv, B_, Nv, Hkv, hd, l0, nl, epi, s);
 }
