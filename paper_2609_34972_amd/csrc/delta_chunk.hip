@@ -479,18 +479,19 @@ __global__ __launch_bounds__(SEG ? 512 : 256) __attribute__((amdgpu_waves_per_eu
 
 // ------------------------------------------------------------------ segments in order
 
-// S <- Phi_g S + Psi_g for g = 1 .. P - 1, from S = Psi_0; grid (Hv, B), 32 state columns per wave. Phi
-// enters the product in bf16, as it is stored; two LDS buffers of it, and Psi one step ahead.
+// S <- Phi_g S + Psi_g for g = 1 .. P - 1, from S = Psi_0; grid (DV / 32, Hv, B), one wave and 32 state
+// columns a block. Phi enters the product in bf16, as it is stored; two LDS buffers of it, and Psi one step
+// ahead. A step is bounded by its loads, so the columns of a head are spread over CUs although each of
+// them then reads all of Phi (32 KiB of 48 a step).
 template <int DK, int DV>
-__global__ __launch_bounds__(256) void k_gdr_join(float* __restrict__ S, int Hv, GdrWs ws) {
+__global__ __launch_bounds__(64) void k_gdr_join(float* __restrict__ S, int Hv, GdrWs ws) {
   using namespace gdc;
   constexpr int NKT = DK / 32, BYTES = DK * DK * 2, INS = BYTES / 1024;
   __shared__ __align__(16) unsigned char smem[2 * BYTES];
   const int P = ws.P;
-  const int64_t seq = (int64_t)blockIdx.y * Hv + blockIdx.x;
-  const int lane = threadIdx.x & 63, wave = wave_index();
-  const int h = lane >> 5, rr = lane & 31, prow = pi(rr), n0 = wave * 32;
-  const bool active = n0 < DV;
+  const int64_t seq = (int64_t)blockIdx.z * Hv + blockIdx.y;
+  const int lane = threadIdx.x;
+  const int h = lane >> 5, rr = lane & 31, prow = pi(rr), n0 = blockIdx.x * 32;
   const float* psi = ws.psi + seq * P * DK * DV + n0 + rr;
   f32x16 st[NKT], ps[NKT];
   auto load_psi = [&](int g, f32x16 (&x)[NKT]) {
@@ -501,17 +502,14 @@ __global__ __launch_bounds__(256) void k_gdr_join(float* __restrict__ S, int Hv,
   };
   auto issue = [&](int g) {
     const bf16* src = (const bf16*)ws.phi + (seq * P + g) * DK * DK;
-    for (int i = wave; i < INS; i += 4) copy_rows<DK>(src, BYTES, smem + (g & 1) * BYTES, i);
+    for (int i = 0; i < INS; ++i) copy_rows<DK>(src, BYTES, smem + (g & 1) * BYTES, i);
   };
-  if (active) {
-    load_psi(0, st);
-    load_psi(1, ps);
-  }
+  load_psi(0, st);
+  load_psi(1, ps);
   issue(1);
   for (int g = 1; g < P; ++g) {
     pipe_sync<waitcnt_imm(0, 0)>();
     if (g + 1 < P) issue(g + 1);
-    if (!active) continue;
     const unsigned char* sm = smem + (g & 1) * BYTES;
     bf16x8 sb[NKT][2];
 #pragma unroll
@@ -529,7 +527,6 @@ __global__ __launch_bounds__(256) void k_gdr_join(float* __restrict__ S, int Hv,
         for (int q = 0; q < 2; ++q)
           mfma_k16(st[kt], lds_b8(sm + row_off<DK>(kt * 32 + prow, 4 * k2 + 2 * q + h)), sb[k2][q]);
   }
-  if (!active) return;
   float* Sg = S + seq * DK * DV + n0 + rr;
 #pragma unroll
   for (int kt = 0; kt < NKT; ++kt)
@@ -562,7 +559,7 @@ static hipError_t chunk_launch(const bf16* k, const bf16* v, const float* alpha,
     k_gdr_scan<DK, DV, true><<<grid, 512, L::BYTES, s>>>(k, v, S, Hk, Hv, N, ws);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_gdr_join<DK, DV><<<dim3(Hv, B), 256, 0, s>>>(S, Hv, ws);
+    k_gdr_join<DK, DV><<<dim3(DV / 32, Hv, B), 64, 0, s>>>(S, Hv, ws);
   } else {
     k_gdr_scan<DK, DV, false><<<grid, 256, L::BYTES, s>>>(k, v, S, Hk, Hv, N, ws);
   }
