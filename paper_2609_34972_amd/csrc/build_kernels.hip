@@ -772,6 +772,14 @@ __device__ __forceinline__ KvTile kv_tile(int rows_by_xcd) {
   return KvTile{(int)blockIdx.z, mt, nt};
 }
 
+// Place of frequency j's (cos, sin) pair in a row of the rotary table (half pairs). A lane of the K/V
+// epilogue takes the eight consecutive frequencies 8 p .. + 7 as four 16-byte loads; pair (j / 2) % 4 of
+// every p lies together, so that one load of the lanes of a row covers one contiguous run (half a row of a
+// 128-wide head at 64-byte steps otherwise: 2855 -> 2752 us on the video's K/V projection).
+__device__ __forceinline__ int rope_place(int j, int half) {
+  return (((j >> 1) & 3) * (half >> 3) + (j >> 3)) * 2 + (j & 1);
+}
+
 // EPI adds the backbone epilogue: the bias joins the scaled product before it is rounded to
 // the call dtype (as the backbone's projection would), then the staged head rows of K get the
 // per-head RMSNorm and the rotary embedding (the partner half of a head is read from the
@@ -839,6 +847,16 @@ __global__ __launch_bounds__(KvP::NT) void k_kv_proj_p(const bf16* __restrict__ 
   const int wm = wave / C::WGN, wn = wave % C::WGN;
   constexpr int EP = kKvEpiPitch;  // bytes per staged row
   unsigned char* ep = smem + wave * (C::WM * EP);
+  // EPI: the bias of this lane's columns, loaded once for all its rows.
+  u32x2 bias4[EPI ? C::FN : 1];
+  if constexpr (EPI) {
+#pragma unroll
+    for (int b = 0; b < C::FN; ++b) {
+      const int n = n0 + wn * C::WN + b * 16 + pipe_col(lane);
+      const bf16* bias = n < kv ? epi.kb : epi.vb;
+      bias4[b] = bias && n < N ? *(const u32x2*)(bias + (int64_t)l * kv + (n < kv ? n : n - kv)) : u32x2{};
+    }
+  }
   __syncthreads();  // every wave is done with the pipeline stages
 #pragma unroll
   for (int a = 0; a < C::FM; ++a) {
@@ -850,14 +868,9 @@ __global__ __launch_bounds__(KvP::NT) void k_kv_proj_p(const bf16* __restrict__ 
       const int cw = b * 16 + pipe_col(lane);  // first of this lane's 4 columns in the wave tile
       float y[4] = {v[0] * rs, v[1] * rs, v[2] * rs, v[3] * rs};
       if constexpr (EPI) {
-        const int n = n0 + wn * C::WN + cw;
-        const bf16* bias = n < kv ? epi.kb : epi.vb;
-        if (bias && n < N) {
-          float bb[4];
-          load4_bf16(bias + (int64_t)l * kv + (n < kv ? n : n - kv), bb);
+        const bf16x4 bb = __builtin_bit_cast(bf16x4, bias4[b]);
 #pragma unroll
-          for (int u = 0; u < 4; ++u) y[u] += bb[u];
-        }
+        for (int u = 0; u < 4; ++u) y[u] += (float)bb[u];
       }
       bf16x4 o = {(bf16)y[0], (bf16)y[1], (bf16)y[2], (bf16)y[3]};
       *(u32x2*)(ep + rw * EP + cw * 2) = __builtin_bit_cast(u32x2, o);
@@ -868,76 +881,107 @@ __global__ __launch_bounds__(KvP::NT) void k_kv_proj_p(const bf16* __restrict__ 
   constexpr int LPR = C::WN / 8;        // lanes per row (8 bf16 each)
   constexpr int RPI = WAVE / LPR;       // rows per store instruction
   const int cpiece = (lane % LPR) * 8;  // first column of this lane's piece
-#pragma unroll 4
-  for (int r0 = 0; r0 < C::WM; r0 += RPI) {
-    const int rw = r0 + lane / LPR;
-    const int row = m0 + wm * C::WM + rw;
-    const int n = n0 + wn * C::WN + cpiece;
-    const bool valid = row < T && n < N;
-    u32x4 v = *(const u32x4*)(ep + rw * EP + cpiece * 2);
-    if constexpr (EPI) {
-      if (epi.kn || epi.rope) {  // uniform: every lane takes the same branch
-        const bool is_k = n < kv;
-        const int ch = (is_k ? n : n - kv) % hd;  // channel of this lane's first column in its head
-        const int half = hd >> 1;
-        float x[8];
-        unpack8(v, x);
-        float sc = 1.f;
-        if (epi.kn) {
-          // Sum of squares over the head: hd/8 lanes hold one head row (16 for hd 128, 8 for 64).
-          float ss = 0.f;
-          if (is_k && valid)
+  const int n = n0 + wn * C::WN + cpiece;
+  const bool is_k = n < kv;
+  const int ch = (is_k ? n : n - kv) % hd;  // channel of this lane's first column in its head
+  const int half = hd >> 1;
+  // EPI: waves without key columns have nothing to normalise or rotate (uniform).
+  const bool k_steps = EPI && (epi.kn || epi.rope) && n0 + wn * C::WN < kv;
+  constexpr int RB = 4;  // rows whose staged pieces (and table entries) are requested together
+  const int pc = ch < half ? ch + half : ch - half;  // EPI: partner channels of this piece
+  u32x4 kn_own = {}, kn_partner = {};
+  if (EPI && k_steps && epi.kn) {
+    kn_own = *(const u32x4*)(epi.kn + (int64_t)l * hd + ch);
+    kn_partner = *(const u32x4*)(epi.kn + (int64_t)l * hd + pc);
+  }
+  // This lane's row walks down the tile by address: a division by Nv and the products of the cache strides
+  // for every row took 42 vector instructions a store, 3% of a tile.
+  const int row1 = m0 + wm * C::WM + lane / LPR;
+  int ii = row1 % Nv;
+  const int o = is_k ? n : n - kv;
+  bf16* dst = (is_k ? Kv : Vv) + (((int64_t)l * B_ + row1 / Nv) * Hkv + o / hd) * head_stride + (int64_t)ii * hd + ch;
+  const int64_t next_seq = (int64_t)(Hkv - 1) * head_stride;  // from a head's end to the same head of the next sequence
+#pragma unroll 1
+  for (int r00 = 0; r00 < C::WM; r00 += RB * RPI) {
+    // The staged pieces of RB rows, and for EPI their partners and (cos, sin), are all requested before the
+    // first is used: one at a time, behind the branches below, every row waited out an LDS or L2 read.
+    u32x4 own[RB], partner[RB];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) ss += x[e] * x[e];
-          ss += shfl_xor(ss, 1);
-          ss += shfl_xor(ss, 2);
-          ss += shfl_xor(ss, 4);
-          if (hd == 128) ss += shfl_xor(ss, 8);
-          sc = rsqrtf(ss / (float)hd + epi.kn_eps);
-        }
-        if (is_k && valid) {
-          if (epi.kn) {
-            float w[8];
-            unpack8(*(const u32x4*)(epi.kn + (int64_t)l * hd + ch), w);
+    for (int u = 0; u < RB; ++u) {
+      const unsigned char* at = ep + (r00 + u * RPI + lane / LPR) * EP;
+      own[u] = *(const u32x4*)(at + cpiece * 2);
+      if (EPI && k_steps && epi.rope) partner[u] = *(const u32x4*)(at + (cpiece + pc - ch) * 2);
+    }
 #pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] *= sc * w[e];
-          }
-          if (epi.rope) {
-            const bool first = ch < half;
-            const int pc = first ? ch + half : ch - half;  // partner channels of this piece
-            float xp[8];
-            unpack8(*(const u32x4*)(ep + rw * EP + (cpiece + pc - ch) * 2), xp);
-            if (epi.kn) {
-              float w[8];
-              unpack8(*(const u32x4*)(epi.kn + (int64_t)l * hd + pc), w);
+    for (int u = 0; u < RB; ++u) asm volatile("" : "+v"(own[u]));  // (read here, not behind the store's condition)
+    f32x4 cs[RB][4];
+    if (EPI && k_steps && epi.rope) {
+      const int j0 = ch < half ? ch : ch - half;
 #pragma unroll
-              for (int e = 0; e < 8; ++e) xp[e] *= sc * w[e];
-            }
-            const int j0 = first ? ch : pc;
-            const f32x4* cs = (const f32x4*)(epi.rope + ((int64_t)row * half + j0) * 2);
+      for (int u = 0; u < RB; ++u) {
+        const int row = min(m0 + wm * C::WM + r00 + u * RPI + lane / LPR, T - 1);
+        const f32x4* t = (const f32x4*)(epi.rope + (int64_t)row * half * 2) + (j0 >> 3);
 #pragma unroll
-            for (int e2 = 0; e2 < 4; ++e2) {
-              const f32x4 t = cs[e2];  // (cos, sin) of frequencies j0 + 2 e2 and j0 + 2 e2 + 1
-#pragma unroll
-              for (int u = 0; u < 2; ++u) {
-                const int e = 2 * e2 + u;
-                const float c = t[2 * u], sn = t[2 * u + 1];
-                x[e] = first ? x[e] * c - xp[e] * sn : x[e] * c + xp[e] * sn;
-              }
-            }
-          }
-          v = pack8(x);
-        }
+        for (int e2 = 0; e2 < 4; ++e2) cs[u][e2] = t[e2 * (half >> 3)];
       }
     }
-    if (!valid) continue;
-    const int bb = row / Nv, ii = row - bb * Nv;
-    bf16* out = n < kv ? Kv : Vv;
-    const int o = n < kv ? n : n - kv;
-    const int h = o / hd, c = o - h * hd;
-    bf16* dst = out + ((int64_t)l * B_ + bb) * Hkv * head_stride + (int64_t)h * head_stride +
-                (int64_t)ii * hd + c;
-    __builtin_nontemporal_store(v, (u32x4*)dst);  // streaming: the caches are read by later launches
+#pragma unroll
+    for (int ru = 0; ru < RB; ++ru) {
+      const bool valid = row1 + r00 + ru * RPI < T && n < N;
+      u32x4 v = own[ru];
+      if constexpr (EPI) {
+        if (k_steps) {
+          float x[8];
+          unpack8(v, x);
+          float sc = 1.f;
+          if (epi.kn) {
+            // Sum of squares over the head: hd/8 lanes hold one head row (16 for hd 128, 8 for 64).
+            float ss = 0.f;
+            if (is_k && valid)
+#pragma unroll
+              for (int e = 0; e < 8; ++e) ss += x[e] * x[e];
+            ss += shfl_xor(ss, 1);
+            ss += shfl_xor(ss, 2);
+            ss += shfl_xor(ss, 4);
+            if (hd == 128) ss += shfl_xor(ss, 8);
+            sc = rsqrtf(ss / (float)hd + epi.kn_eps);
+          }
+          if (is_k && valid) {
+            if (epi.kn) {
+              float w[8];
+              unpack8(kn_own, w);
+#pragma unroll
+              for (int e = 0; e < 8; ++e) x[e] *= sc * w[e];
+            }
+            if (epi.rope) {
+              const bool first = ch < half;
+              float xp[8];
+              unpack8(partner[ru], xp);
+              if (epi.kn) {
+                float w[8];
+                unpack8(kn_partner, w);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) xp[e] *= sc * w[e];
+              }
+#pragma unroll
+              for (int e2 = 0; e2 < 4; ++e2) {
+                const f32x4 t = cs[ru][e2];  // (cos, sin) of frequencies j0 + 2 e2 and j0 + 2 e2 + 1
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                  const int e = 2 * e2 + u;
+                  const float c = t[2 * u], sn = t[2 * u + 1];
+                  x[e] = first ? x[e] * c - xp[e] * sn : x[e] * c + xp[e] * sn;
+                }
+              }
+            }
+            v = pack8(x);
+          }
+        }
+      }
+      if (valid) __builtin_nontemporal_store(v, (u32x4*)dst);  // streaming: read by later launches
+      dst += RPI * hd;
+      for (ii += RPI; ii >= Nv; ii -= Nv) dst += next_seq;
+    }
   }
 }
 
@@ -989,7 +1033,7 @@ __global__ __launch_bounds__(256) void k_kv_epi_post(T* __restrict__ Kv, T* __re
   }
   if (!valid) return;
   if (epi.rope) {
-    const f32x2 cs = *(const f32x2*)(epi.rope + (((int64_t)b * Nv + i) * HALF + j) * 2);
+    const f32x2 cs = *(const f32x2*)(epi.rope + (((int64_t)b * Nv + i) * HALF + rope_place(j, HALF)) * 2);
     const float a = k1 * cs[0] - k2 * cs[1];
     k2 = k2 * cs[0] + k1 * cs[1];
     k1 = a;
@@ -1000,7 +1044,8 @@ __global__ __launch_bounds__(256) void k_kv_epi_post(T* __restrict__ Kv, T* __re
   }
 }
 
-// (cos, sin) of the rotary angle for every (token, frequency); fp64 angle and functions.
+// (cos, sin) of the rotary angle for every (token, frequency), in the order of rope_place; fp64 angle and
+// functions.
 __global__ __launch_bounds__(256) void k_rope_table(const int32_t* __restrict__ pos, int B_, int Nv,
                                                     int half, int s0, int s1, double log_theta,
                                                     float* __restrict__ table) {
@@ -1015,7 +1060,7 @@ __global__ __launch_bounds__(256) void k_rope_table(const int32_t* __restrict__ 
   const double ang = p * exp(-(double)j / (double)half * log_theta);
   double sn, cs;
   sincos(ang, &sn, &cs);
-  *(f32x2*)(table + idx * 2) = f32x2{(float)cs, (float)sn};
+  *(f32x2*)(table + (t * half + rope_place(j, half)) * 2) = f32x2{(float)cs, (float)sn};
 }
 
 hipError_t launch_rope_table(const int32_t* pos, int B_, int Nv, int hd, int s0, int s1,

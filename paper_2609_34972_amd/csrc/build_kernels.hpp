@@ -40,13 +40,14 @@ struct KvEpiArgs {
   const void* v_bias = nullptr;  // [L, Hkv*hd], call dtype
   const void* k_norm = nullptr;  // [L, hd], call dtype
   float k_norm_eps = 0.f;
-  const float* rope = nullptr;   // [T][hd/2] (cos, sin) pairs from launch_rope_table
+  const float* rope = nullptr;   // T rows of hd/2 (cos, sin) pairs from launch_rope_table
   bool any() const { return k_bias || v_bias || k_norm || rope; }
 };
 
 // cos/sin table of the rotary embedding for every visual token: entry (t, j) for token
 // t = b*Nv + i turns by pos[b][a][i] * theta^(-2j/hd), a = position axis of frequency j
-// (sections s0, s1, s2 of hd/2 frequencies). table holds T*hd/2 (cos, sin) float pairs.
+// (sections s0, s1, s2 of hd/2 frequencies). table holds T*hd/2 (cos, sin) float pairs, those of a token in
+// the order that the projection's epilogue reads.
 hipError_t launch_rope_table(const int32_t* pos, int B, int Nv, int hd, int s0, int s1,
                              float theta, float* table, hipStream_t s);
 
