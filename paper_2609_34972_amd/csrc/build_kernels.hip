@@ -302,7 +302,7 @@ __global__ __launch_bounds__(C::NT) void k_down_act_p(const bf16* __restrict__ E
       const int l = n / r, j = n - l * r;
       const f32x4& v = acc[a][b];
       store4_bf16(Z + ((int64_t)l * T + row) * r + j, v[0], v[1], v[2], v[3],
-                  [](float x) { return ACT == 0 ? silu(x) : gelu(x); });
+                  [](float x) { return ACT == 0 ? silu_rcp(x) : gelu(x); });
     }
   }
 }
