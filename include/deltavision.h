@@ -123,14 +123,18 @@ int32_t dv_project_visual_kv_fused(int32_t d, int32_t r, int32_t Hkv, int32_t hd
  * dv_project_visual_kv_ex, dv_kept_visual_kv); both compute Eq. 5 and the RMSNorm statistics of
  * Eq. 7 with the same products in the same order, so M_l * gamma_l is the same to the bit and
  * only the order in which the row sum of squares is added up differs.
- *   1 (tiled): each block computes a 128 x 128 tile of M_l for up to four layers.
- *   2 (Z-resident): each block takes 128 rows of one layer, keeps their Z_l in registers and
- *     walks all of d, streaming only U_l; for r = 256 or 512 (other ranks take the tiled kernel).
- *   0 (default): the Z-resident kernel where r is 256 and there are at least eight rounds
- *     (2048) of its blocks (ceil(B*Nv / 128) * nl), else the tiled kernel.
+ *   1 (tiled): each block computes a 128 x 128 tile of M_l for up to eight layers.
+ *   2 (Z-resident): each block takes 256 rows of one layer, keeps their Z_l in registers and
+ *     walks d or a part of it, streaming only U_l and E; for r = 256 or 512 (other ranks take the
+ *     tiled kernel).
+ *   0 (default): the Z-resident kernel where r is 256 and ceil(B*Nv / 128) * nl is at least 2048,
+ *     and for other calls with r = 256 or 512 where it is expected to take less time; else the
+ *     tiled kernel.
  * dv_set_up_kernel(mode) selects, process-wide (a call already enqueued keeps its kernel);
- * mode must be 0, 1 or 2. dv_project_visual_kv_up_kernel returns the kernel (1 or 2) a bf16 call
- * with these sizes takes under the current setting, 1 for any other dtype; no GPU work.
+ * mode must be 0, 1 or 2. dv_project_visual_kv_up_kernel returns, for a bf16 call with these
+ * sizes under the current setting, 2 where the mode or the r = 256 size rule requires the
+ * Z-resident kernel and 1 otherwise (under mode 0 also for the calls that take it by time), 1 for
+ * any other dtype; no GPU work.
  */
 dv_status dv_set_up_kernel(int32_t mode);
 int32_t dv_project_visual_kv_up_kernel(int64_t T, int32_t d, int32_t r, int32_t nl, int32_t dtype);

@@ -61,8 +61,10 @@ hipError_t launch_project_kv(const void* E, const void* Z, const void* Uw, const
                              bool first_group, bool last_group, const KvEpiArgs* epi = nullptr);
 
 // Which kernel computes M_l * gamma_l and the row sums of squares for the bf16 projection:
-// 0 picks by shape (the Z-resident kernel for r = 256 once there are at least eight rounds of its
-// blocks), 1 always the tiled kernel, 2 the Z-resident kernel wherever it applies (r = 256, 512).
+// 0 picks by shape (the Z-resident kernel for r = 256 from 2048 tiles of 128 rows on, and for r = 256 or
+// 512 where its rounds of blocks are expected to take less time), 1 always the tiled kernel, 2 the
+// Z-resident kernel wherever it applies (r = 256, 512). up_z_resident is what the public query reports:
+// the first rule or the mode, not the choice by time.
 void set_up_kernel(int mode);
 bool up_z_resident(int64_t T, int d, int r, int nl);
 
