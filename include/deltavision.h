@@ -121,8 +121,8 @@ int32_t dv_project_visual_kv_fused(int32_t d, int32_t r, int32_t Hkv, int32_t hd
 /*
  * Kernel for M_l * gamma_l and the row sums of squares in the bf16 projection (dv_project_visual_kv,
  * dv_project_visual_kv_ex, dv_kept_visual_kv); both compute Eq. 5 and the RMSNorm statistics of
- * Eq. 7 with the same products in the same order, so M_l * gamma_l is the same to the bit and
- * only the order in which the row sum of squares is added up differs.
+ * Eq. 7 with the same products and sums in the same order, so M_l * gamma_l, K and V are the
+ * same to the bit.
  *   1 (tiled): each block computes a 128 x 128 tile of M_l for up to eight layers.
  *   2 (Z-resident): each block takes 256 rows of one layer, keeps their Z_l in registers and
  *     walks d or a part of it, streaming only U_l and E; for r = 256 or 512 (other ranks take the

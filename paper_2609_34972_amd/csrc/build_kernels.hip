@@ -442,8 +442,8 @@ __global__ __launch_bounds__(C::NT) void k_up_norm_p(const bf16* __restrict__ E,
 // 64-column tiles; each of its eight waves (two per SIMD) keeps its 32 rows of Z_l in registers (r / 4 of
 // them), so only U and E stream. Against the 128 x 128 tiles of k_up_norm_p, which load both operands for
 // every 64 of K and meet a barrier there, a column tile needs a quarter of the loads into LDS and one
-// barrier for its whole K, and the waves see whole rows of M. What bounded the first versions was the
-// latency of E behind U's loads, then:
+// barrier for its whole K. Bound by U's and the stores' traffic beside the MFMAs (1666 us at 16384 tokens,
+// r = 512; 1283 without U's loads, 1374 without the stores, 1538 with half the MFMAs):
 // * U: a whole column tile (64 x r, 64 KiB at r = 512) per stage, two stages; tile j + 1 is requested when
 //   every wave is past tile j - 1. E: the wave's own 4 KiB, requested as soon as the tile before has left
 //   the buffer (which also turns M * gamma around for the stores), so ahead of U's next tile.
@@ -456,11 +456,11 @@ __global__ __launch_bounds__(C::NT) void k_up_norm_p(const bf16* __restrict__ E,
 // * The stores' column offset is in the vector offset. With it in the scalar offset the compiler takes
 //   the data registers as free at once, and a register overwritten by the next instruction was stored
 //   with its new value.
-// M * gamma is the tiled kernel's to the bit; the row sums of squares are added up in another order.
-// Measured (us, tiled -> this kernel): Qwen2.5-VL video (r = 512) 16384 tokens 2153 -> 1660, 4096 576 ->
-// 474, 1024 165 -> 133; d = 4096, r = 256, 32 layers: 5760 tokens 693 -> 675, and the K/V projection after
-// it, with one partial sum per row to read instead of 32, 9688 -> 9628. 1660 us are 1.0 PFLOP/s and
-// 2.0 TB/s of stores.
+// M * gamma and the row sums of squares (one per 128 columns, its two halves added last) are the tiled
+// kernel's to the bit, so K and V do not depend on which kernel a call takes.
+// Measured (us, tiled -> this kernel): Qwen2.5-VL video (r = 512) 16384 tokens 2170 -> 1714, 2304 350 ->
+// 277, 1024 172 -> 142; d = 4096, r = 256, 32 layers: 2880 tokens 361 -> 335, 5760 691 and 694, 8192
+// 1000 -> 942. 1714 us are 0.98 PFLOP/s and 1.9 TB/s of stores.
 namespace upz {
 constexpr int BM = 256, BN = 64, NW = 8, WM = 32, FM = WM / 16, FN = BN / 16;
 constexpr int SCR_PITCH = BN + 8;  // bf16 per row of the store turnaround
@@ -586,7 +586,8 @@ __global__ __launch_bounds__(upz::NW * 64) __attribute__((amdgpu_waves_per_eu(2,
   bf16* scr = (bf16*)ebuf;
   // E in the accumulator layout: row a*16 + lane % 16, chunk 2b + lane / 32 of the swizzled row.
   const int eo = (lane & 15) * 128 + (((lane >> 5) ^ ((lane & 15) >> 1)) << 4) + 8 * ((lane >> 4) & 1);
-  float ss[FM] = {};
+  float half[FM] = {};  // row sums of an even column tile, until the odd one's join them
+  const int np = (d / BN + 1) / 2;
   auto epilogue = [&](int j) {
     u32x2 e4[FM][FN];
 #pragma unroll
@@ -599,6 +600,7 @@ __global__ __launch_bounds__(upz::NW * 64) __attribute__((amdgpu_waves_per_eu(2,
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
     for (int a = 0; a < FM; ++a) {
+      float ss = 0.f;
 #pragma unroll
       for (int b = 0; b < FN; ++b) {
         const bf16x4 e = __builtin_bit_cast(bf16x4, e4[a][b]);
@@ -607,11 +609,17 @@ __global__ __launch_bounds__(upz::NW * 64) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const float m = acc[a][b][u] + (float)e[u];
-          ss[a] += m * m;
+          ss += m * m;
           o[u] = (bf16)(m * (float)g[u]);
         }
         *(u32x2*)(scr + (lane & 15) * SCR_PITCH + b * 16 + 4 * (lane >> 4)) = __builtin_bit_cast(u32x2, o);
       }
+      ss += shfl_xor(ss, 16);
+      ss += shfl_xor(ss, 32);
+      const bool odd = j & 1;
+      if ((odd || j + 1 == ncol) && lane < 16 && row + 16 * a < left)
+        ssq[((int64_t)lz * np + (c0 + j) / 2) * T + m0 + row + 16 * a] = odd ? half[a] + ss : ss;
+      half[a] = ss;
       // The buffer is this wave's own: LDS serves a wave's accesses in order.
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
@@ -672,13 +680,6 @@ __global__ __launch_bounds__(upz::NW * 64) __attribute__((amdgpu_waves_per_eu(2,
     epilogue(ncol - 1);
   }
   __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));  // the zero-filling loads past the last tile
-#pragma unroll
-  for (int a = 0; a < FM; ++a) {
-    float s = ss[a];
-    s += shfl_xor(s, 16);
-    s += shfl_xor(s, 32);
-    if (lane < 16 && row + 16 * a < left) ssq[((int64_t)lz * gridDim.z + blockIdx.z) * T + m0 + row + 16 * a] = s;
-  }
 }
 
 // Backbone epilogue arguments as the kernels see them (see KvEpiArgs).
@@ -1250,7 +1251,7 @@ void set_up_kernel(int mode) { g_up_kernel.store(mode, std::memory_order_relaxed
 
 // Columns per block of the Z-resident kernel for these sizes, in 64-column tiles: the count whose rounds of
 // 256 blocks end first, a block costing its tiles plus four for its start (Z). *cost: that time, in column
-// tiles. At least two tiles, so that a row has no more partial sums than the tiled kernel writes.
+// tiles. An even count, so that a block sums whole 128-column parts of a row.
 // Measured (us) for 1, 2, 4, 8 blocks per row: 4096 tokens of d = 3584, r = 512, 28 layers 474, 494, 488,
 // 541; 1024 tokens 211, 133, 141, 159; 2304 of d = 4096, r = 256, 32 layers 401, 339, 323, 327.
 static int up_z_columns(int64_t T, int d, int nl, int64_t* cost) {
@@ -1259,7 +1260,7 @@ static int up_z_columns(int64_t T, int d, int nl, int64_t* cost) {
   int best = ncol;
   *cost = 0;
   for (int nb = 1; nb <= std::max(1, std::min(16, ncol / 2)); ++nb) {
-    const int cpb = cdiv(ncol, nb);
+    const int cpb = 2 * cdiv(ncol, 2 * nb);
     const int64_t c = cdiv(bands * cdiv(ncol, cpb), 256) * (int64_t)(cpb + 4);
     if (nb == 1 || c < *cost) {
       best = cpb;
@@ -1285,14 +1286,14 @@ bool up_z_resident(int64_t T, int d, int r, int nl) {
 }
 
 // Whether a call takes the Z-resident kernel: as above, or by time. A column tile of it takes 4.0 us at
-// r = 512 and 3.3 at r = 256 (420, 120 and 32 tiles in a row: 1676, 474 and 133 us; 204 and 100: 675 and
-// 323), a round of 512 blocks of the tiled kernel 11 and 8 us (196, 49 and 13 rounds: 2153, 576 and 165 us;
+// r = 512 and 3.4 at r = 256 (420, 120 and 32 tiles in a row: 1714, 474 and 142 us; 272, 204 and 100: 942,
+// 694 and 323), a round of 512 blocks of the tiled kernel 11 and 8 us (196, 49 and 13 rounds: 2153, 576 and 165 us;
 // 90 and 36: 693 and 301).
 static bool up_z_taken(int64_t T, int d, int r, int nl, int64_t cost) {
   if (up_z_resident(T, d, r, nl)) return true;
   if (g_up_kernel.load(std::memory_order_relaxed) != 0 || !up_z_applies(T, d, r)) return false;
   const int64_t rounds = cdiv((int64_t)cdiv(T, UpP::BM) * cdiv(d, UpP::BN) * nl, 512);
-  return r == 512 ? cost * 40 < rounds * 110 : cost * 33 < rounds * 80;
+  return r == 512 ? cost * 40 < rounds * 110 : cost * 34 < rounds * 80;
 }
 
 static hipError_t kv_launch_bf16(const void* E, const void* Z, const void* Uw, const void* gamma,
@@ -1323,10 +1324,10 @@ static hipError_t kv_launch_bf16(const void* E, const void* Z, const void* Uw, c
   int64_t zcost;
   const int cpb = up_z_columns(T_, d, nl, &zcost);
   const bool zres = up_z_taken(T_, d, r, nl, zcost);
-  const int np = zres ? cdiv(d / upz::BN, cpb) : cdiv(d, UpP::BN);  // sums of squares per row
+  const int np = cdiv(d, UpP::BN);  // sums of squares per row
   if (first) record(ev.up[0], s);
   if (zres) {
-    const dim3 gz(cdiv(T_, upz::BM), nl, np);
+    const dim3 gz(cdiv(T_, upz::BM), nl, cdiv(d / upz::BN, cpb));
     if (r == 512)
       k_up_norm_zr<512><<<gz, dim3(upz::NW * 64), upz::Lds<512>::BYTES, s>>>(
           (const bf16*)E, (const bf16*)Z, (const bf16*)Uw, (const bf16*)gamma, (bf16*)Mg, ssq, T_, d, l0, cpb);
