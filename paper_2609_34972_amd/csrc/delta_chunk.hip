@@ -420,6 +420,14 @@ __global__ __launch_bounds__(SEG ? 512 : 256) __attribute__((amdgpu_waves_per_eu
       for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
         for (int q = 0; q < 2; ++q) mfma_k16(u[tt], kf[tt][kt][q], sb[kt][q]);
+    // K's first transposed fragments, requested behind the last of these MFMAs instead of after U's (six
+    // layers of 16384 tokens, 32 heads: 768 -> 762 us)
+    s16x4 kv[2][16];
+    auto read_kt = [&](int k2) {
+      const uint32_t lo[2] = {so + ka[0][k2], so + ka[0][k2 + 1]}, hi[2] = {so + ka[1][k2], so + ka[1][k2 + 1]};
+      tr_read16<0, 16 * DK * 2, 32 * DK * 2, 48 * DK * 2>(lo, hi, kv[(k2 / 2) & 1]);
+    };
+    read_kt(0);
     // X = V - gamma (K S)
     bf16x8 xb[2][2];
 #pragma unroll
@@ -451,14 +459,13 @@ __global__ __launch_bounds__(SEG ? 512 : 256) __attribute__((amdgpu_waves_per_eu
       for (int q = 0; q < 2; ++q) ub[tt][q] = acc_bf8(w[tt], q);
 #pragma unroll
     for (int k2 = 0; k2 < NKT; k2 += 2) {
-      s16x4 kv[16];
-      const uint32_t lo[2] = {so + ka[0][k2], so + ka[0][k2 + 1]}, hi[2] = {so + ka[1][k2], so + ka[1][k2 + 1]};
-      tr_read16<0, 16 * DK * 2, 32 * DK * 2, 48 * DK * 2>(lo, hi, kv);
+      const s16x4(&f)[16] = kv[(k2 / 2) & 1];
 #pragma unroll
       for (int x = 0; x < 4; ++x)
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk)
-          mfma_k16(st[k2 + kk], tr_frag(kv[kk * 8 + x * 2], kv[kk * 8 + x * 2 + 1]), ub[x >> 1][x & 1]);
+          mfma_k16(st[k2 + kk], tr_frag(f[kk * 8 + x * 2], f[kk * 8 + x * 2 + 1]), ub[x >> 1][x & 1]);
+      if (k2 + 2 < NKT) read_kt(k2 + 2);
     }
   }
   if (!active) return;
