@@ -1105,12 +1105,13 @@ static int up_layers_per_block(int64_t tiles_per_layer, int nl) {
   return best;
 }
 
-// Whether an fp32 call with this many 64 x 64 tiles takes the small-call kernels (small_f32.hip). Measured
-// (us, 64 x 64 tiles against the small kernels, a launch of about 4 us included): down projection 13.2 ->
-// 7.1 at 1 tile, 26.6 -> 17.2 at 60, 32.7 -> 20.7 at 64, 172 -> 273 at 288; K/V 14.0 -> 7.2 at 32 tiles,
-// 28.6 -> 14.0 at 48, 14.0 -> 12.8 and 126.9 -> 127.9 at 128, 32.6 -> 60.8 at 480; up projection 8.8 ->
-// 6.3 at 16, 9.9 -> 8.2 at 144, 17.1 -> 20.6 at 256 (r = 256), 15.6 -> 21.3 at 512.
-constexpr int64_t kSmallTiles = 96, kSmallUpTiles = 160;
+// Whether an fp32 launch with this many 64 x 64 tiles takes the small-call kernels (small_f32.hip). They give the
+// tile kernels' bits, so the rule may count all layers of a launch: groups, ranges and kept layers agree with
+// the all-layer call on either side of it. Measured (us, a launch of about 4 us included, 64 x 64 tiles against
+// the small kernels): down 11.4 -> 6.2 at 1 tile (d 256), 107 -> 38 at 1 (d 4096), 31.6 -> 21.0 at 64 (d 1024);
+// K/V 14.2 -> 7.7 at 32 and 14.5 -> 13.4 at 96 (d 256), 125 -> 76 at 64 and 126 -> 123 at 128 (d 4096), 15.1 ->
+// 21.7 at 192; up 9.2 -> 6.6 at 16, 11.9 -> 9.2 at 110, 17.3 -> 14.2 at 330, 19.7 -> 23.2 at 720 (r 16 and 64).
+bool small_f32(int64_t tiles, bool up) { return tiles <= (up ? 160 : 96); }
 
 template <typename T>
 static hipError_t down_launch(const void* E, const void* Dw, void* Z, int T_, int d, int L, int r,
@@ -1118,7 +1119,7 @@ static hipError_t down_launch(const void* E, const void* Dw, void* Z, int T_, in
   typedef typename BuildTiles<T>::Down C;
   dim3 grid(cdiv((int64_t)L * r, C::BN), cdiv(T_, C::BM));
   record(ev.down[0], s);
-  if ((int64_t)grid.x * grid.y <= kSmallTiles) {
+  if (small_f32((int64_t)grid.x * grid.y, false)) {
     const hipError_t e = launch_small_down((const float*)E, (const float*)Dw, (float*)Z, T_, d, L, r, act, s);
     record(ev.down[1], s);
     return e;
@@ -1233,7 +1234,7 @@ hipError_t launch_kv_only(const void* Mg, const float* ssq, const void* Wk, cons
   typedef typename BuildTiles<float>::KV CK;
   dim3 gk(cdiv(2 * Hkv * hd, CK::BN), cdiv(T_, CK::BM), nl);
   record(ev.kv[0], s);
-  if ((int64_t)gk.x * gk.y * gk.z <= kSmallTiles) {
+  if (small_f32((int64_t)gk.x * gk.y * gk.z, false)) {
     const hipError_t e = launch_small_kv((const float*)Mg, ssq, (const float*)Wk, (const float*)Wv, (float*)Kv,
                                          (float*)Vv, B_, Nv, d, Hkv, hd, l0, nl, np, eps, s);
     record(ev.kv[1], s);
@@ -1374,7 +1375,7 @@ static hipError_t kv_launch(const void* E, const void* Z, const void* Uw, const 
   dim3 gu(np, cdiv(T_, CU::BM), nl);
   if (first) record(ev.up[0], s);
   hipError_t e = hipSuccess;
-  if (f32 && (int64_t)gu.x * gu.y * gu.z <= kSmallUpTiles) {
+  if (f32 && small_f32((int64_t)gu.x * gu.y * gu.z, true)) {
     e = launch_small_up((const float*)E, (const float*)Z, (const float*)Uw, (const float*)gamma, (float*)Mg, ssq, T_, d,
                         r, l0, nl, s);
   } else {
@@ -1385,7 +1386,7 @@ static hipError_t kv_launch(const void* E, const void* Z, const void* Uw, const 
   if (e != hipSuccess) return e;
   dim3 gk(cdiv(2 * Hkv * hd, CK::BN), cdiv(T_, CK::BM), nl);
   if (first) record(ev.kv[0], s);
-  if (f32 && (int64_t)gk.x * gk.y * gk.z <= kSmallTiles) {
+  if (f32 && small_f32((int64_t)gk.x * gk.y * gk.z, false)) {
     e = launch_small_kv((const float*)Mg, ssq, (const float*)Wk, (const float*)Wv, (float*)Kv, (float*)Vv, B_, Nv, d,
                         Hkv, hd, l0, nl, np, eps, s);
   } else {

@@ -68,6 +68,10 @@ hipError_t launch_project_kv(const void* E, const void* Z, const void* Uw, const
 void set_up_kernel(int mode);
 bool up_z_resident(int64_t T, int d, int r, int nl);
 
+// Launch rule of the fp32 kernels for small calls: tiles is the launch's count of 64 x 64 tiles, up for the up
+// projection (else the down or the K/V projection).
+bool small_f32(int64_t tiles, bool up);
+
 // The fused kernel (fused_kv.hip) computes M_l, its RMSNorm and the K/V projection of 64 tokens
 // in one block and needs no workspace. It covers bf16, 2 Hkv hd = 1024, r in {128, 256, 512},
 // d a multiple of 64, no backbone epilogue (up_kv_fused_eligible), and the projection takes it

@@ -4,6 +4,8 @@ import sys
 import numpy as np
 import torch
 
+import paper_2609_34972_amd as dvl
+
 # Parity bar: normwise max relative error ||x - ref||_inf / ||ref||_inf per output
 # tensor (and per layer), 1e-4 for fp32 runs and 2e-2 for bf16 runs.
 TOL = {"f32": 1e-4, "bf16": 2e-2}
@@ -37,3 +39,11 @@ def f64(t: torch.Tensor) -> np.ndarray:
 
 def cuda(t: torch.Tensor) -> torch.Tensor:
     return t.to("cuda:0").contiguous()
+
+
+def launch_rule(name: str, restype, *args):
+    """A launch rule of the library (a C++ function of namespace dv, by its mangled name), called on
+    (ctypes type, value) pairs: tests that need a certain kernel assert that their sizes reach it."""
+    f = getattr(dvl.load(), name)
+    f.restype, f.argtypes = restype, [t for t, _ in args]
+    return f(*(v for _, v in args))
