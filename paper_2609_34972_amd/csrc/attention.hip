@@ -1276,7 +1276,12 @@ __global__ __launch_bounds__(ksplit::NWAVE * 64) void k_attn_ksplit(AttnArgs a, 
 #pragma unroll
     for (int e4 = 0; e4 < 4; ++e4) {
       f32x4 v = *(const f32x4*)(o + e4 * 4);
-      if (DEC) v += *(const f32x4*)(o + 16 * MPITCH + e4 * 4);
+      if constexpr (DEC) {
+        // The low parts add nothing to an infinite sum (theirs, with parts of either sign or zero, is NaN).
+        const f32x4 v_low = *(const f32x4*)(o + 16 * MPITCH + e4 * 4);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = __builtin_isfinite(v[u]) ? v[u] + v_low[u] : v[u];
+      }
 #pragma unroll
       for (int u = 0; u < 4; ++u) out[e4 * 4 + u] += v[u] * sc[w];
     }
