@@ -323,7 +323,7 @@ __global__ __launch_bounds__(f32rows::waves<HD>() * 64) void k_attn_f32(AttnArgs
     for (int j = 0; j < J; ++j) q[j] = *(const f32x4*)(qr + 16 * j);
   }
   f32x4 kf[J], vf[H2][4];
-  auto load = [&](int t) {  // keys past the end: the last one again, masked below
+  auto load = [&](int t) {  // keys past the end: the last one again, its score masked and its V cleared below
     const int kj = min(t + ln, k_end - 1);
     const float* kp = (kj < a.Nv ? Kvb + (int64_t)kj * HD : Ktb + (int64_t)(kj - a.Nv) * HD) + 4 * kg;
 #pragma unroll
@@ -355,6 +355,13 @@ __global__ __launch_bounds__(f32rows::waves<HD>() * 64) void k_attn_f32(AttnArgs
     for (int h = 0; h < H2; ++h)
 #pragma unroll
       for (int r = 0; r < 4; ++r) vc[h][r] = vf[h][r];
+    if (t + 16 > k_end) {  // past the end: zeros, since probability 0 times an infinite last V is not 0
+#pragma unroll
+      for (int h = 0; h < H2; ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (t + 4 * kg + r >= k_end) vc[h][r] = f32x4{};
+    }
     if (t + NW * 16 < k_end) load(t + NW * 16);
     float mx = m;
 #pragma unroll

@@ -1,6 +1,7 @@
 """Infinite V entries (a cache whose projection overflowed): an output that gives such a key a positive
-probability is that infinity, in every kernel that multiplies by more than the probability itself. GQA decode
-(probabilities in two bf16 parts, the second of either sign or zero): keys at the edges of their tiles, the
+probability is that infinity, in every kernel that multiplies by more than the probability itself or pads a
+key tile. GQA decode (probabilities in two bf16 parts, the second of either sign or zero) and the fp32
+kernel for few rows (16-key tiles whose tail repeats the last key): keys at the edges of their tiles, the
 last visual key and the last key of all, with and without a key split. All other outputs are finite and
 meet the parity bar."""
 import numpy as np
@@ -13,9 +14,11 @@ from tests.gpu_helpers import TOL, cuda, f64, say
 
 pytestmark = pytest.mark.gpu
 
-# dtype, B, Hq, Hkv, hd, Nv, q_pos0 (one query): the last two split their keys given room
+# dtype, B, Hq, Hkv, hd, Nv, q_pos0 (one query): the last two of each dtype split their keys given room
 CASES = [("bf16", 1, 4, 2, 128, 40, 5), ("bf16", 2, 14, 2, 128, 0, 33), ("bf16", 1, 8, 1, 128, 1000, 70),
-         ("bf16", 2, 28, 4, 128, 4099, 9)]
+         ("bf16", 2, 28, 4, 128, 4099, 9),
+         ("f32", 1, 9, 1, 64, 17, 5), ("f32", 2, 18, 2, 128, 0, 20), ("f32", 1, 16, 1, 64, 1000, 3),
+         ("f32", 1, 10, 1, 128, 2003, 9)]
 
 
 @pytest.mark.parametrize("split", [True, False], ids=["ws", "nows"])
