@@ -131,10 +131,9 @@ int32_t dv_project_visual_kv_fused(int32_t d, int32_t r, int32_t Hkv, int32_t hd
  *     and for other calls with r = 256 or 512 where it is expected to take less time; else the
  *     tiled kernel.
  * dv_set_up_kernel(mode) selects, process-wide (a call already enqueued keeps its kernel);
- * mode must be 0, 1 or 2. dv_project_visual_kv_up_kernel returns, for a bf16 call with these
- * sizes under the current setting, 2 where the mode or the r = 256 size rule requires the
- * Z-resident kernel and 1 otherwise (under mode 0 also for the calls that take it by time), 1 for
- * any other dtype; no GPU work.
+ * mode must be 0, 1 or 2. dv_project_visual_kv_up_kernel returns the kernel (1 or 2) a bf16 call with
+ * these sizes takes under the current setting (with a workspace for its nl layers; a smaller one
+ * chooses for each group of layers), 1 for any other dtype; no GPU work.
  */
 dv_status dv_set_up_kernel(int32_t mode);
 int32_t dv_project_visual_kv_up_kernel(int64_t T, int32_t d, int32_t r, int32_t nl, int32_t dtype);

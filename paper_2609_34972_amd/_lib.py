@@ -250,8 +250,7 @@ def set_up_kernel(mode: int) -> None:
 
 
 def project_visual_kv_up_kernel(T: int, d: int, r: int, nl: int, dtype: torch.dtype) -> int:
-    """2 where the mode or the r = 256 size rule requires the Z-resident kernel for a projection
-    call with these sizes, else 1 (by default also for calls that take it because it is faster)."""
+    """The kernel (1 tiled, 2 Z-resident) a projection call with these sizes takes now."""
     code = DV_BF16 if dtype == torch.bfloat16 else DV_F32
     return int(load().dv_project_visual_kv_up_kernel(int(T), int(d), int(r), int(nl), code))
 

@@ -188,7 +188,8 @@ dv_status dv_set_up_kernel(int32_t mode) {
 int32_t dv_project_visual_kv_up_kernel(int64_t T, int32_t d, int32_t r, int32_t nl,
                                        int32_t dtype) {
   if (T <= 0 || d <= 0 || r <= 0 || nl <= 0 || dtype != DV_BF16) return 1;
-  return dv::up_z_resident(T, d, r, nl) ? 2 : 1;
+  int cpb;
+  return dv::up_z_taken(T, d, r, nl, &cpb) ? 2 : 1;
 }
 
 }  // extern "C"

@@ -1256,13 +1256,13 @@ void set_up_kernel(int mode) { g_up_kernel.store(mode, std::memory_order_relaxed
 // Measured (us) for 1, 2, 4, 8 blocks per row: 4096 tokens of d = 3584, r = 512, 28 layers 474, 494, 488,
 // 541; 1024 tokens 211, 133, 141, 159; 2304 of d = 4096, r = 256, 32 layers 401, 339, 323, 327.
 static int up_z_columns(int64_t T, int d, int nl, int64_t* cost) {
-  const int ncol = d / upz::BN;
-  const int64_t bands = (int64_t)cdiv(T, upz::BM) * nl;
+  const int ncol = std::max(1, d / upz::BN);
+  const int64_t bands = (T + upz::BM - 1) / upz::BM * nl;
   int best = ncol;
   *cost = 0;
   for (int nb = 1; nb <= std::max(1, std::min(16, ncol / 2)); ++nb) {
     const int cpb = 2 * cdiv(ncol, 2 * nb);
-    const int64_t c = cdiv(bands * cdiv(ncol, cpb), 256) * (int64_t)(cpb + 4);
+    const int64_t c = (bands * cdiv(ncol, cpb) + 255) / 256 * (cpb + 4);
     if (nb == 1 || c < *cost) {
       best = cpb;
       *cost = c;
@@ -1274,26 +1274,27 @@ static int up_z_columns(int64_t T, int d, int nl, int64_t* cost) {
 // 32-bit buffer offsets: E, M * gamma and Z_l within 2^31 bytes, U_l below the out-of-range offset of the
 // tile stream.
 static bool up_z_applies(int64_t T, int d, int r) {
-  return (r == 256 || r == 512) && T * d * 2 < (int64_t(1) << 31) && T * r * 2 < (int64_t(1) << 31) &&
-         (int64_t)d * r * 2 < (int64_t(1) << 30);
+  constexpr int64_t most = (int64_t(1) << 30) - 1;  // elements
+  return (r == 256 || r == 512) && T <= most / d && T <= most / r && (int64_t)d * r * 2 < (int64_t(1) << 30);
 }
 
-// The part of the rule that the public query reports: forced, or r = 256 with at least 2048 tiles of 128
-// rows (eight rounds).
-bool up_z_resident(int64_t T, int d, int r, int nl) {
+// Whether a call takes the Z-resident kernel. By default, where its rounds of blocks are expected to take
+// less time: a column tile of it takes 4.0 us at r = 512 and 3.4 at r = 256 (420, 120 and 32 tiles in a row:
+// 1714, 474 and 142 us; 272, 204 and 100: 942, 694 and 323), a round of 512 blocks of the tiled kernel 11 and
+// 8 us (196, 49 and 13 rounds: 2153, 576 and 165 us; 90 and 36: 691 and 301). The estimate is good to about 5%:
+// at 5760 tokens of d = 4096, r = 256, 32 layers it takes the Z-resident kernel (664 and 692 us tiled, 680 and
+// 694 resident, on two cards), at 4096 tokens too (503 and 513).
+// With r = 256 and at least 2048 tiles of 128 rows (eight rounds) it is taken whatever the estimate says, which
+// there is too high for a small d (us, tiled and resident): 9000 tokens of d = 1024, 32 layers 301 and 246;
+// 11607 of d = 512, 28 layers 171 and 164; 8800 of d = 3584, 30 layers 840 and 773; only 6757 of d = 256, 48
+// layers 94 and 100.
+bool up_z_taken(int64_t T, int d, int r, int nl, int* cpb) {
   const int mode = g_up_kernel.load(std::memory_order_relaxed);
   if (mode == 1 || !up_z_applies(T, d, r)) return false;
-  return mode == 2 || (r == 256 && (int64_t)cdiv(T, 128) * nl >= 8 * 256);
-}
-
-// Whether a call takes the Z-resident kernel: as above, or by time. A column tile of it takes 4.0 us at
-// r = 512 and 3.4 at r = 256 (420, 120 and 32 tiles in a row: 1714, 474 and 142 us; 272, 204 and 100: 942,
-// 694 and 323), a round of 512 blocks of the tiled kernel 11 and 8 us (196, 49 and 13 rounds: 2153, 576 and 165 us;
-// 90 and 36: 693 and 301).
-static bool up_z_taken(int64_t T, int d, int r, int nl, int64_t cost) {
-  if (up_z_resident(T, d, r, nl)) return true;
-  if (g_up_kernel.load(std::memory_order_relaxed) != 0 || !up_z_applies(T, d, r)) return false;
-  const int64_t rounds = cdiv((int64_t)cdiv(T, UpP::BM) * cdiv(d, UpP::BN) * nl, 512);
+  int64_t cost;
+  *cpb = up_z_columns(T, d, nl, &cost);
+  if (mode == 2 || (r == 256 && (int64_t)cdiv(T, 128) * nl >= 8 * 256)) return true;
+  const int64_t rounds = ((T + UpP::BM - 1) / UpP::BM * cdiv(d, UpP::BN) * nl + 511) / 512;
   return r == 512 ? cost * 40 < rounds * 110 : cost * 34 < rounds * 80;
 }
 
@@ -1322,9 +1323,8 @@ static hipError_t kv_launch_bf16(const void* E, const void* Z, const void* Uw, c
     return e;
   }
   const int T_ = B_ * Nv;
-  int64_t zcost;
-  const int cpb = up_z_columns(T_, d, nl, &zcost);
-  const bool zres = up_z_taken(T_, d, r, nl, zcost);
+  int cpb = 0;
+  const bool zres = up_z_taken(T_, d, r, nl, &cpb);
   const int np = cdiv(d, UpP::BN);  // sums of squares per row
   if (first) record(ev.up[0], s);
   if (zres) {

@@ -63,10 +63,10 @@ hipError_t launch_project_kv(const void* E, const void* Z, const void* Uw, const
 // Which kernel computes M_l * gamma_l and the row sums of squares for the bf16 projection:
 // 0 picks by shape (the Z-resident kernel for r = 256 from 2048 tiles of 128 rows on, and for r = 256 or
 // 512 where its rounds of blocks are expected to take less time), 1 always the tiled kernel, 2 the
-// Z-resident kernel wherever it applies (r = 256, 512). up_z_resident is what the public query reports:
-// the first rule or the mode, not the choice by time.
+// Z-resident kernel wherever it applies (r = 256, 512). up_z_taken: whether a launch of nl layers takes it
+// now, and its columns per block in 64-column tiles.
 void set_up_kernel(int mode);
-bool up_z_resident(int64_t T, int d, int r, int nl);
+bool up_z_taken(int64_t T, int d, int r, int nl, int* cpb);
 
 // Launch rule of the fp32 kernels for small calls: tiles is the launch's count of 64 x 64 tiles, up for the up
 // projection (else the down or the K/V projection).
