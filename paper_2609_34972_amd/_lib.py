@@ -406,8 +406,9 @@ def delta_rule_write(k, v, alpha, beta, S, ws: Optional[torch.Tensor] = None, st
     return S
 
 
-# A pure function of its sizes, asked for at every call without a workspace; bounded.
-@lru_cache(maxsize=256)
+# A pure function of its sizes, asked for at every call without a workspace; bounded. Typed: sizes that the
+# library refuses (4.0) are not answered from those it took (4).
+@lru_cache(maxsize=256, typed=True)
 def text_visual_attention_workspace(B: int, Hq: int, Hkv: int, hd: int, Nv: int, Nq: int,
                                     Nkt: int) -> int:
     return int(load().dv_text_visual_attention_workspace(B, Hq, Hkv, hd, Nv, Nq, Nkt))

@@ -191,6 +191,17 @@ def test_attention_workspace_query(lib):
     assert lib.dv_text_visual_attention_workspace(1, 6, 4, 128, 10, 4, 4) == 0  # invalid GQA
 
 
+def test_attention_workspace_refuses_other_types_before_and_after(lib):
+    sizes = (1, 28, 4, 128, 771, 2, 5)
+    for first in (True, False):
+        for bad in (771.0, "771"):
+            with pytest.raises(ctypes.ArgumentError):
+                _lib.text_visual_attention_workspace(*sizes[:4], bad, *sizes[5:])
+        if first:
+            assert _lib.text_visual_attention_workspace(*sizes) == \
+                lib.dv_text_visual_attention_workspace(*sizes)
+
+
 def rec_call(lib, ws=FAKE, ws_bytes=None, **over):
     a = dict(E=FAKE, Dw=FAKE, Uw=FAKE, g=FAKE, Wk=FAKE, Wv=FAKE, Kv=FAKE, Vv=FAKE, B=1, Nv=64,
              d=256, L=4, r=16, Hkv=4, hd=64, act=0, eps=1e-5, dt=F32)
