@@ -318,7 +318,7 @@ struct UpLds {
 };
 
 
-// One 128 x 128 tile of M_l * gamma_l for kUpLayers consecutive layers through one pipeline
+// One 128 x 128 tile of M_l * gamma_l for lpb consecutive layers through one pipeline
 // (the next layer's first operand tiles load while a layer's epilogue runs). The epilogue works
 // on the accumulators in place: lane l holds row l % 16 of each 16-row fragment and four
 // consecutive columns, E and gamma are fetched in that layout, the per-row sum of squares of fp32
@@ -1073,9 +1073,11 @@ static TileOrder up_order() { return TileOrder{8, 8}; }
 // blocks balance worse over the CUs. Of 1 to 8 layers the count is taken whose blocks, dealt in order
 // to the 512 slots (two per CU), end first, a block costing its layers plus 0.7 for its start.
 // Measured (us, 17 layers of d = 4096, r = 256, eight layers a block against this rule): 64 tokens
-// 40 -> 17, 256 45 -> 32, 576 58 -> 49. Full launches keep eight (ms): Qwen2.5-VL video 2.27 with 4
-// layers, 2.18 with 8, 2.28-2.40 with 14, 16 or 28; LLaVA-7B 0.31 with 4 or 8, 0.33 with 16.
-static int up_layers_per_block(int64_t tiles_per_layer, int nl) {
+// 40 -> 17, 256 45 -> 32, 576 50 -> 42. Launches of several rounds gain less from longer blocks: LLaVA-7B
+// (576 tiles a layer, 32 layers) 302 with 4, 294 with the 6 that the rule takes, 300 with 8, 330 with 16;
+// Qwen2.5-VL video (3584 tiles, 28 layers; this kernel forced) 2270 with 4, 2180 with the rule's 8, 2280-2400
+// with 14, 16 or 28.
+int up_layers_per_block(int64_t tiles_per_layer, int nl) {
   const int64_t slots = 512;
   int best = 1;
   double best_end = 0.0;
@@ -1143,23 +1145,31 @@ static hipError_t down_run(DownKernel kernel, int bm, int bn, int nt, int lds, c
   return hipGetLastError();
 }
 
+// At most one 128 x 128 tile per CU: four stages instead of two keep three K tiles in flight where no second
+// block covers a load's latency (T 64 to 768 of 17 LLaVA layers: 60-66 -> 38-46 us). With more tiles than CUs
+// the two-stage blocks, two to a CU, are faster.
+// Otherwise three tile shapes; each is priced as rounds of its block slots times the outputs a CU
+// computes per round, and the cheapest wins, ties going to the larger tile (fewer operand
+// bytes per MFMA): 256 x 256 (one block per CU), 192 x 128 with eight waves and 128 x 128
+// with four (two blocks per CU each; two 192 x 128 blocks take all 160 KiB of LDS, and forcing
+// one per CU made them 25-35% slower). LLaVA-7B's 2304 x 8192 takes 1.5 rounds of 192 x 128
+// (0.180 -> 0.149 ms against the earlier 96 x 128 blocks, bit-identical), LLaVA-NeXT's 23040 x
+// 8192 15 rounds of 192 x 128 instead of 11.25 of 256 x 256 (1.47 -> 1.31-1.41 ms), and
+// Qwen2.5-VL video's 16384 x 14336 14 whole rounds of 256 x 256.
+DownTiles down_tiles(int64_t T, int64_t N) {
+  auto tiles = [&](int bm, int bn) { return (int64_t)cdiv(N, bn) * cdiv(T, bm); };
+  const int64_t t128 = tiles(DownP::BM, DownP::BN);
+  if (t128 <= 256) return DownTiles::k128Deep;
+  const int64_t c256 = (int64_t)cdiv(tiles(KvP::BM, KvP::BN), 256) * 256 * 256;
+  const int64_t c192 = (int64_t)cdiv(tiles(DownP192::BM, DownP192::BN), 512) * 2 * 192 * 128;
+  const int64_t c128 = (int64_t)cdiv(t128, 512) * 2 * 128 * 128;
+  if (c256 <= c192 && c256 <= c128) return DownTiles::k256;
+  return c192 <= c128 ? DownTiles::k192 : DownTiles::k128;
+}
+
 hipError_t launch_down_act(const void* E, const void* Dw, void* Z, int64_t T_, int d, int L,
                            int r, int act, int dtype, hipStream_t s, const LaunchEvents& ev) {
   if (dtype == 1) {
-    // Otherwise three tile shapes; each is priced as rounds of its block slots times the outputs a CU
-    // computes per round, and the cheapest wins, ties going to the larger tile (fewer operand
-    // bytes per MFMA): 256 x 256 (one block per CU), 192 x 128 with eight waves and 128 x 128
-    // with four (two blocks per CU each; two 192 x 128 blocks take all 160 KiB of LDS, and forcing
-    // one per CU made them 25-35% slower). LLaVA-7B's 2304 x 8192 takes 1.5 rounds of 192 x 128
-    // (0.180 -> 0.149 ms against the earlier 96 x 128 blocks, bit-identical), LLaVA-NeXT's 23040 x
-    // 8192 15 rounds of 192 x 128 instead of 11.25 of 256 x 256 (1.47 -> 1.31-1.41 ms), and
-    // Qwen2.5-VL video's 16384 x 14336 14 whole rounds of 256 x 256.
-    const int64_t N = (int64_t)L * r;
-    const int64_t t128 = (int64_t)cdiv(N, DownP::BN) * cdiv(T_, DownP::BM);
-    const int64_t c256 = (int64_t)cdiv(cdiv(N, KvP::BN) * cdiv(T_, KvP::BM), 256) * 256 * 256;
-    const int64_t c192 =
-        (int64_t)cdiv(cdiv(N, DownP192::BN) * cdiv(T_, DownP192::BM), 512) * 2 * 192 * 128;
-    const int64_t c128 = (int64_t)cdiv(t128, 512) * 2 * 128 * 128;
     constexpr int kDeep = 4, kDeepLds = kDeep * DownP::STAGE * 2;
     static bool once = [] {
       allow_lds(k_down_act_p<KvP, 0, 2>, KvP::LDS_BYTES);
@@ -1172,20 +1182,21 @@ hipError_t launch_down_act(const void* E, const void* Dw, void* Z, int64_t T_, i
     }();
     (void)once;
     const bool silu = act == 0;
-    // At most one 128 x 128 tile per CU: four stages instead of two keep three K tiles in flight where
-    // no second block covers a load's latency (T 64 to 768 of 17 LLaVA layers: 60-66 -> 38-46 us). With more
-    // tiles than CUs the two-stage blocks, two to a CU, are faster.
-    if (t128 <= 256)
-      return down_run(silu ? k_down_act_p<DownP, 0, kDeep> : k_down_act_p<DownP, 1, kDeep>, DownP::BM, DownP::BN,
-                      DownP::NT, kDeepLds, E, Dw, Z, (int)T_, d, L, r, s, ev);
-    if (c256 <= c192 && c256 <= c128)
-      return down_run(silu ? k_down_act_p<KvP, 0, 2> : k_down_act_p<KvP, 1, 2>, KvP::BM, KvP::BN, KvP::NT,
-                      KvP::LDS_BYTES, E, Dw, Z, (int)T_, d, L, r, s, ev);
-    if (c192 <= c128)
-      return down_run(silu ? k_down_act_p<DownP192, 0, 2> : k_down_act_p<DownP192, 1, 2>, DownP192::BM, DownP192::BN,
-                      DownP192::NT, DownP192::LDS_BYTES, E, Dw, Z, (int)T_, d, L, r, s, ev);
-    return down_run(silu ? k_down_act_p<DownP, 0, 2> : k_down_act_p<DownP, 1, 2>, DownP::BM, DownP::BN, DownP::NT,
-                    DownP::LDS_BYTES, E, Dw, Z, (int)T_, d, L, r, s, ev);
+    switch (down_tiles(T_, (int64_t)L * r)) {
+      case DownTiles::k128Deep:
+        return down_run(silu ? k_down_act_p<DownP, 0, kDeep> : k_down_act_p<DownP, 1, kDeep>, DownP::BM, DownP::BN,
+                        DownP::NT, kDeepLds, E, Dw, Z, (int)T_, d, L, r, s, ev);
+      case DownTiles::k256:
+        return down_run(silu ? k_down_act_p<KvP, 0, 2> : k_down_act_p<KvP, 1, 2>, KvP::BM, KvP::BN, KvP::NT,
+                        KvP::LDS_BYTES, E, Dw, Z, (int)T_, d, L, r, s, ev);
+      case DownTiles::k192:
+        return down_run(silu ? k_down_act_p<DownP192, 0, 2> : k_down_act_p<DownP192, 1, 2>, DownP192::BM,
+                        DownP192::BN, DownP192::NT, DownP192::LDS_BYTES, E, Dw, Z, (int)T_, d, L, r, s, ev);
+      case DownTiles::k128:
+        return down_run(silu ? k_down_act_p<DownP, 0, 2> : k_down_act_p<DownP, 1, 2>, DownP::BM, DownP::BN, DownP::NT,
+                        DownP::LDS_BYTES, E, Dw, Z, (int)T_, d, L, r, s, ev);
+    }
+    return hipErrorInvalidValue;
   }
   return down_launch<float>(E, Dw, Z, (int)T_, d, L, r, act, s, ev);
 }

@@ -68,6 +68,12 @@ hipError_t launch_project_kv(const void* E, const void* Z, const void* Uw, const
 void set_up_kernel(int mode);
 bool up_z_taken(int64_t T, int d, int r, int nl, int* cpb);
 
+// Launch rules of the bf16 build: tile shape of the down projection of T tokens to N = L r columns (128 x 128
+// in four stages; 256 x 256, 192 x 128 or 128 x 128 in two), and layers per block of the tiled up projection.
+enum class DownTiles : int { k128Deep, k256, k192, k128 };
+DownTiles down_tiles(int64_t T, int64_t N);
+int up_layers_per_block(int64_t tiles_per_layer, int nl);
+
 // Launch rule of the fp32 kernels for small calls: tiles is the launch's count of 64 x 64 tiles, up for the up
 // projection (else the down or the K/V projection).
 bool small_f32(int64_t tiles, bool up);

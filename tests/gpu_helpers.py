@@ -1,4 +1,5 @@
 """Shared helpers of the GPU parity tests (tolerances, error metrics, input staging)."""
+import ctypes
 import sys
 
 import numpy as np
@@ -47,3 +48,17 @@ def launch_rule(name: str, restype, *args):
     f = getattr(dvl.load(), name)
     f.restype, f.argtypes = restype, [t for t, _ in args]
     return f(*(v for _, v in args))
+
+
+# Tile shapes of the bf16 down projection (the library's DownTiles).
+DOWN_DEEP, DOWN_256, DOWN_192, DOWN_128 = range(4)
+
+
+def down_tiles(T: int, N: int) -> int:
+    return launch_rule("_ZN2dv10down_tilesEll", ctypes.c_int, (ctypes.c_int64, T), (ctypes.c_int64, N))
+
+
+def up_layers_per_block(T: int, d: int, nl: int) -> int:
+    """Layers that a block of the tiled bf16 up projection takes in a launch of nl."""
+    tiles = -(-T // 128) * -(-d // 128)
+    return launch_rule("_ZN2dv19up_layers_per_blockEli", ctypes.c_int, (ctypes.c_int64, tiles), (ctypes.c_int, nl))

@@ -10,7 +10,7 @@ import torch
 import oracle
 import paper_2609_34972_amd as dvl
 from paper_2609_34972_amd import configs, synth
-from tests.gpu_helpers import assert_close, cuda, f64, say
+from tests.gpu_helpers import DOWN_192, assert_close, cuda, down_tiles, f64, say, up_layers_per_block
 
 pytestmark = pytest.mark.gpu
 
@@ -118,6 +118,7 @@ def test_down_192_row_tiles_ragged():
     w = configs.LLAVA7B.with_(name="mid_down192", d=256, L=16, r=256, Hq=2, Hkv=2, hd=64, B=3,
                               Nv=700, Nt=8, outlier_channels=(3, 200))
     say(f"[down 192-row tiles {w.name}: T {w.T} x N {w.L * w.r} x d {w.d}]")
+    assert down_tiles(w.T, w.L * w.r) == DOWN_192
     E, wts = gen_build(w, seed=13)
     Eg, Dg = cuda(E), cuda(wts["Dw"])
     Z = torch.empty(w.L, w.T, w.r, dtype=Eg.dtype, device="cuda:0")
@@ -129,12 +130,13 @@ def test_down_192_row_tiles_ragged():
 
 
 def test_project_kv_eleven_layers_in_runs_of_eight():
-    """The tiled up projection takes up to eight layers per block: 11 layers run as blocks of 8
-    and 3, the sub-range l0 = 2, nl = 9 as 8 and 1, and a one-layer workspace as single layers.
+    """The tiled up projection takes up to eight layers per block: at 300 tiles a layer 11 layers run as
+    blocks of 8 and 3, the sub-range l0 = 2, nl = 9 as 6 and 3, and a one-layer workspace as single layers.
     All three give the same bytes, and the all-layer call matches the oracle layer by layer."""
-    w = configs.LLAVA7B.with_(name="mid_eleven_layers", d=512, L=11, r=64, Hq=4, Hkv=4, hd=128,
-                              B=2, Nv=150, Nt=8, outlier_channels=(7, 311))
+    w = configs.LLAVA7B.with_(name="mid_eleven_layers", d=512, L=11, r=64, Hq=2, Hkv=2, hd=64,
+                              B=2, Nv=4765, Nt=8, outlier_channels=(7, 311))
     say(f"[eleven layers {w.name}: T {w.T}, d {w.d}, r {w.r}]")
+    assert [up_layers_per_block(w.T, w.d, nl) for nl in (11, 9, 1)] == [8, 6, 1]
     E, wts = gen_build(w, seed=9)
     Eg, wg = cuda(E), {k: cuda(v) for k, v in wts.items()}
     Z, Kv, Vv = run_build(w, Eg, wg, w.act)
