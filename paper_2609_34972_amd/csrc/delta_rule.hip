@@ -17,8 +17,7 @@
 // columns of the fp32 state, all dk rows, in MFMA accumulators, and since those accumulators
 // (and those of U) are already the B operands of the next product in a permuted k order, a
 // wave's chain needs no exchange with other waves; the block only shares the chunk record in LDS.
-// These are the fp32 kernels; bf16 calls take those of delta_chunk.hip. Products read the state rounded to the call dtype; the
-// state itself stays fp32.
+// The kernels here are fp32; bf16 calls take those of delta_chunk.hip.
 //
 // Long sequences use a two-level scan. The chunk step is affine in S, so a run of chunks maps
 // a start state S to Phi S + Psi: the segments of ws.cps chunks run at once, from the start
@@ -40,15 +39,12 @@ constexpr int C = 64;     // tokens per chunk
 constexpr int NT = 256;   // threads per block (4 waves)
 }  // namespace gdr
 
-template <typename T>
-__device__ __forceinline__ typename Frag8<T>::type frag_load(const T* p) {
-  typedef typename Frag8<T>::type F;
-  return *(const F*)p;
+__device__ __forceinline__ f32x8 frag_load(const float* p) {
+  return *(const f32x8*)p;
 }
 
-template <typename T>
-__device__ __forceinline__ typename Frag8<T>::type frag_zero() {
-  return typename Frag8<T>::type{};
+__device__ __forceinline__ f32x8 frag_zero() {
+  return f32x8{};
 }
 
 // Fragment order. One 32x32x16 MFMA step takes from lane half h the 8 values at k = 8 h .. 8 h + 7
@@ -64,40 +60,38 @@ __device__ __forceinline__ int frag_pos(int m) { return (m & ~12) | ((m & 4) << 
 
 // Element offset of logical position pos in row `row` of a fragment-order matrix of INNER
 // values per row.
-template <typename T, int INNER>
+template <int INNER>
 __device__ __forceinline__ int frag_off(int row, int pos) {
-  constexpr int EPC = 16 / (int)sizeof(T), CPR = INNER / EPC;
+  constexpr int EPC = 4, CPR = INNER / EPC;
   static_assert(CPR == 8 || CPR == 16 || CPR == 32, "row of 8, 16 or 32 chunks");
   const int key = CPR >= 16 ? (row & 15) : ((row >> 1) & 7);
   return row * INNER + (((pos / EPC) ^ key) * EPC) + pos % EPC;
 }
 
 // The 8 values at logical positions 8 g .. 8 g + 7 of row `row`.
-template <typename T, int INNER>
-__device__ __forceinline__ typename Frag8<T>::type frag_get(const T* m, int row, int g) {
-  typedef typename Frag8<T>::type F;
-  const f32x4 lo = *(const f32x4*)(m + frag_off<T, INNER>(row, 8 * g));
-  const f32x4 hi = *(const f32x4*)(m + frag_off<T, INNER>(row, 8 * g + 4));
-  return F{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+template <int INNER>
+__device__ __forceinline__ f32x8 frag_get(const float* m, int row, int g) {
+  const f32x4 lo = *(const f32x4*)(m + frag_off<INNER>(row, 8 * g));
+  const f32x4 hi = *(const f32x4*)(m + frag_off<INNER>(row, 8 * g + 4));
+  return f32x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 }
 
-template <typename T, int INNER>
-__device__ __forceinline__ void frag_put(T* m, int row, int g, typename Frag8<T>::type x) {
-  *(f32x4*)(m + frag_off<T, INNER>(row, 8 * g)) = f32x4{x[0], x[1], x[2], x[3]};
-  *(f32x4*)(m + frag_off<T, INNER>(row, 8 * g + 4)) = f32x4{x[4], x[5], x[6], x[7]};
+template <int INNER>
+__device__ __forceinline__ void frag_put(float* m, int row, int g, f32x8 x) {
+  *(f32x4*)(m + frag_off<INNER>(row, 8 * g)) = f32x4{x[0], x[1], x[2], x[3]};
+  *(f32x4*)(m + frag_off<INNER>(row, 8 * g + 4)) = f32x4{x[4], x[5], x[6], x[7]};
 }
 
-// Items 8 q .. 8 q + 7 of an accumulator tile, rounded to T: a B fragment in fragment order.
-template <typename T>
-__device__ __forceinline__ typename Frag8<T>::type acc_frag(const f32x16& a, int q) {
-  typename Frag8<T>::type x;
+// Items 8 q .. 8 q + 7 of an accumulator tile: a B fragment in fragment order.
+__device__ __forceinline__ f32x8 acc_frag(const f32x16& a, int q) {
+  f32x8 x;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) x[e] = from_f32<T>(a[8 * q + e]);
+  for (int e = 0; e < 8; ++e) x[e] = a[8 * q + e];
   return x;
 }
 
 // Per-chunk record of the workspace: -W [C][DK], Kt [DK][C], Uv^T [DV][C], all in fragment order.
-template <typename T, int DK, int DV>
+template <int DK, int DV>
 struct GdrRec {
   static constexpr int C = gdr::C;
   static constexpr int KT = C * DK, UV = 2 * C * DK, ELEMS = C * (2 * DK + DV);
@@ -106,24 +100,21 @@ struct GdrRec {
 // The chunk's K and V transposed in LDS ([channel][token], 64 tokens a row): 16-byte chunks of a
 // row XOR-swizzled by the row, so that the 16 rows one fragment load touches fall in distinct
 // bank groups without padding.
-template <typename T>
 __device__ __forceinline__ int vk_off(int n, int s) {
-  constexpr int EPC = 16 / (int)sizeof(T), CPR = gdr::C / EPC;
+  constexpr int EPC = 4, CPR = gdr::C / EPC;
   const int key = CPR >= 16 ? (n & 15) : ((n >> 1) & 7);
   return n * gdr::C + (((s / EPC) ^ key) * EPC) + s % EPC;
 }
 
 // 8 consecutive tokens s0 .. s0 + 7 (s0 a multiple of 8) of row n.
-template <typename T>
-__device__ __forceinline__ typename Frag8<T>::type vk_frag(const T* m, int n, int s0) {
-  typedef typename Frag8<T>::type F;
-  const f32x4 lo = *(const f32x4*)(m + vk_off<T>(n, s0));
-  const f32x4 hi = *(const f32x4*)(m + vk_off<T>(n, s0 + 4));
-  return F{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+__device__ __forceinline__ f32x8 vk_frag(const float* m, int n, int s0) {
+  const f32x4 lo = *(const f32x4*)(m + vk_off(n, s0));
+  const f32x4 hi = *(const f32x4*)(m + vk_off(n, s0 + 4));
+  return f32x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 }
 
 // LDS layout of k_gdr_prep (byte offsets). M holds A and is turned into T = (I + A)^-1 in place.
-template <typename T, int DK, int DV>
+template <int DK, int DV>
 struct GdrLds {
   static constexpr int C = gdr::C;
   static constexpr int MP = C + 4;                                 // fp32 pitch of M (bank spread)
@@ -132,8 +123,8 @@ struct GdrLds {
   static constexpr size_t bg = beta + C * 4;                       // float[C]  beta_t gamma_t
   static constexpr size_t m = bg + C * 4;                          // float[C][MP]
   static constexpr size_t vt = m + (size_t)C * MP * 4;             // T[DV][C]  V^T
-  static constexpr size_t kt = vt + (size_t)DV * C * sizeof(T);    // T[DK][C]  K^T
-  static constexpr size_t bytes = kt + (size_t)DK * C * sizeof(T);
+  static constexpr size_t kt = vt + (size_t)DV * C * sizeof(float);    // T[DK][C]  K^T
+  static constexpr size_t bytes = kt + (size_t)DK * C * sizeof(float);
 };
 
 // D[16x16] += A[16x4] B[4x16] in fp32; lane l gives A[l % 16][l / 16] and B[l / 16][l % 16] and
@@ -160,23 +151,22 @@ __device__ __forceinline__ void put16(float* M, int r0, int c0, f32x4 d, float s
   for (int r = 0; r < 4; ++r) M[(r0 + 4 * (lane >> 4) + r) * MP + c0 + (lane & 15)] = sign * d[r];
 }
 
-template <typename T, int DK, int DV>
-__global__ __launch_bounds__(gdr::NT) void k_gdr_prep(const T* __restrict__ k,
-                                                      const T* __restrict__ v,
+template <int DK, int DV>
+__global__ __launch_bounds__(gdr::NT) void k_gdr_prep(const float* __restrict__ k,
+                                                      const float* __restrict__ v,
                                                       const float* __restrict__ alpha,
                                                       const float* __restrict__ beta, int Hk,
                                                       int Hv, int N, GdrWs ws) {
   using namespace gdr;
-  typedef GdrLds<T, DK, DV> L;
-  typedef typename Frag8<T>::type F;
+  typedef GdrLds<DK, DV> L;
   constexpr int MP = L::MP;
   extern __shared__ __align__(16) unsigned char smem[];
   float* g = (float*)(smem + L::g);
   float* bet = (float*)(smem + L::beta);
   float* bgm = (float*)(smem + L::bg);
   float* M = (float*)(smem + L::m);
-  T* VT = (T*)(smem + L::vt);
-  T* KT = (T*)(smem + L::kt);
+  float* VT = (float*)(smem + L::vt);
+  float* KT = (float*)(smem + L::kt);
 
   const int c = blockIdx.x, hv = blockIdx.y, b = blockIdx.z;
   const int NC = (N + C - 1) / C;
@@ -184,8 +174,8 @@ __global__ __launch_bounds__(gdr::NT) void k_gdr_prep(const T* __restrict__ k,
   const int64_t t0 = (int64_t)c * C;
   const int nval = (int)min((int64_t)C, (int64_t)N - t0);
   const int64_t seq = (int64_t)b * Hv + hv;  // (sequence, value head)
-  const T* kc = k + (((int64_t)b * Hk + hk) * N + t0) * DK;
-  const T* vc = v + (seq * N + t0) * DV;
+  const float* kc = k + (((int64_t)b * Hk + hk) * N + t0) * DK;
+  const float* vc = v + (seq * N + t0) * DV;
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
   const int h = lane >> 5, rr = lane & 31;
 
@@ -201,26 +191,26 @@ __global__ __launch_bounds__(gdr::NT) void k_gdr_prep(const T* __restrict__ k,
   }
   // Piece idx covers token idx % C and channels 8 (idx / C) .. + 7: consecutive lanes take
   // consecutive tokens, so the transposed LDS writes below are contiguous runs.
-  F vpc[VP], kpc[KP];
+  f32x8 vpc[VP], kpc[KP];
 #pragma unroll
   for (int q = 0; q < VP; ++q) {
     const int idx = tid + q * NT, sidx = idx % C, n0 = (idx / C) * 8;
-    vpc[q] = sidx < nval ? frag_load<T>(vc + (int64_t)sidx * DV + n0) : frag_zero<T>();
+    vpc[q] = sidx < nval ? frag_load(vc + (int64_t)sidx * DV + n0) : frag_zero();
   }
 #pragma unroll
   for (int q = 0; q < KP; ++q) {
     const int idx = tid + q * NT, sidx = idx % C, n0 = (idx / C) * 8;
-    kpc[q] = sidx < nval ? frag_load<T>(kc + (int64_t)sidx * DK + n0) : frag_zero<T>();
+    kpc[q] = sidx < nval ? frag_load(kc + (int64_t)sidx * DK + n0) : frag_zero();
   }
   const int ti3 = wave == 0 ? 0 : 1, si3 = wave == 2 ? 1 : 0;  // K K^T tile of waves 0..2
-  F fa3[DK / 16], fb3[DK / 16];
+  f32x8 fa3[DK / 16], fb3[DK / 16];
   if (wave < 3) {
     const int ta = ti3 * 32 + rr, sb = si3 * 32 + rr;
 #pragma unroll
     for (int ks = 0; ks < DK / 16; ++ks) {
       const int ko = ks * 16 + h * 8;
-      fa3[ks] = ta < nval ? frag_load<T>(kc + (int64_t)ta * DK + ko) : frag_zero<T>();
-      fb3[ks] = sb < nval ? frag_load<T>(kc + (int64_t)sb * DK + ko) : frag_zero<T>();
+      fa3[ks] = ta < nval ? frag_load(kc + (int64_t)ta * DK + ko) : frag_zero();
+      fb3[ks] = sb < nval ? frag_load(kc + (int64_t)sb * DK + ko) : frag_zero();
     }
   }
 
@@ -242,13 +232,13 @@ __global__ __launch_bounds__(gdr::NT) void k_gdr_prep(const T* __restrict__ k,
   for (int q = 0; q < VP; ++q) {
     const int idx = tid + q * NT, sidx = idx % C, n0 = (idx / C) * 8;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) VT[vk_off<T>(n0 + e, sidx)] = vpc[q][e];
+    for (int e = 0; e < 8; ++e) VT[vk_off(n0 + e, sidx)] = vpc[q][e];
   }
 #pragma unroll
   for (int q = 0; q < KP; ++q) {
     const int idx = tid + q * NT, sidx = idx % C, n0 = (idx / C) * 8;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) KT[vk_off<T>(n0 + e, sidx)] = kpc[q][e];
+    for (int e = 0; e < 8; ++e) KT[vk_off(n0 + e, sidx)] = kpc[q][e];
   }
   __syncthreads();
   const float gC = g[C - 1];
@@ -297,17 +287,17 @@ __global__ __launch_bounds__(gdr::NT) void k_gdr_prep(const T* __restrict__ k,
   } else {
     // Kt in fragment order: logical positions 8 gq .. 8 gq + 7 of row n hold tokens
     // frag_pos(8 gq + e), two runs of four.
-    T* Kt = ws.rec<T>(seq * NC + c) + GdrRec<T, DK, DV>::KT;
+    float* Kt = ws.rec<float>(seq * NC + c) + GdrRec<DK, DV>::KT;
     for (int idx = tid - 64; idx < DK * (C / 8); idx += NT - 64) {
       const int n = idx / (C / 8), gq = idx % (C / 8);
       const int tq = (gq >> 1) * 16 + (gq & 1) * 4;
-      F y;
+      f32x8 y;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int t = tq + (e >> 2) * 8 + (e & 3);
-        y[e] = from_f32<T>(__expf(gC - g[t]) * to_f32(KT[vk_off<T>(n, t)]));
+        y[e] = __expf(gC - g[t]) * KT[vk_off(n, t)];
       }
-      frag_put<T, C>(Kt, n, gq, y);
+      frag_put<C>(Kt, n, gq, y);
     }
   }
   __syncthreads();
@@ -331,7 +321,7 @@ __global__ __launch_bounds__(gdr::NT) void k_gdr_prep(const T* __restrict__ k,
 
   // 5. Uv = (T diag(beta)) V and W = (T diag(beta gamma)) K: waves 0, 1 the Uv row tiles 0, 1 and
   //    waves 2, 3 the W row tiles, each over every column tile. The scaled rows of T are formed
-  //    in the call dtype as they are read (row tile 0 of T is zero beyond column 31). Uv comes
+  //    as they are read (row tile 0 of T is zero beyond column 31). Uv comes
   //    out with a value column per lane and W, computed as K^T (T diag(beta gamma))^T, with a
   //    token per lane, so both store rows of their fragment-order form (Uv^T and -W): items
   //    8 q .. 8 q + 7 of a tile are logical positions 16 q + 8 h .. + 7 of the lane's row.
@@ -339,7 +329,7 @@ __global__ __launch_bounds__(gdr::NT) void k_gdr_prep(const T* __restrict__ k,
     const bool isu = wave < 2;
     const int ti = wave & 1, nks = ti == 0 ? 2 : 4;
     const float* sc = isu ? bet : bgm;
-    F tf[4];
+    f32x8 tf[4];
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       if (ks < nks) {
@@ -348,12 +338,12 @@ __global__ __launch_bounds__(gdr::NT) void k_gdr_prep(const T* __restrict__ k,
         const f32x4 slo = *(const f32x4*)(sc + ks * 16 + h * 8), shi = *(const f32x4*)(sc + ks * 16 + h * 8 + 4);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          tf[ks][e] = from_f32<T>(lo[e] * slo[e]);
-          tf[ks][e + 4] = from_f32<T>(hi[e] * shi[e]);
+          tf[ks][e] = lo[e] * slo[e];
+          tf[ks][e + 4] = hi[e] * shi[e];
         }
       }
     }
-    T* rec = ws.rec<T>(seq * NC + c);
+    float* rec = ws.rec<float>(seq * NC + c);
     const int nd = isu ? DV / 32 : DK / 32;
     for (int ni = 0; ni < nd; ++ni) {
       f32x16 acc = {};
@@ -361,19 +351,19 @@ __global__ __launch_bounds__(gdr::NT) void k_gdr_prep(const T* __restrict__ k,
       for (int ks = 0; ks < 4; ++ks) {
         if (ks < nks) {
           if (isu)
-            mfma_k16(acc, tf[ks], vk_frag<T>(VT, ni * 32 + rr, ks * 16 + h * 8));
+            mfma_k16(acc, tf[ks], vk_frag(VT, ni * 32 + rr, ks * 16 + h * 8));
           else
-            mfma_k16(acc, vk_frag<T>(KT, ni * 32 + rr, ks * 16 + h * 8), tf[ks]);
+            mfma_k16(acc, vk_frag(KT, ni * 32 + rr, ks * 16 + h * 8), tf[ks]);
         }
       }
       if (isu) {
 #pragma unroll
         for (int qh = 0; qh < 2; ++qh)
-          frag_put<T, C>(rec + GdrRec<T, DK, DV>::UV, ni * 32 + rr, ti * 4 + 2 * qh + h, acc_frag<T>(acc, qh));
+          frag_put<C>(rec + GdrRec<DK, DV>::UV, ni * 32 + rr, ti * 4 + 2 * qh + h, acc_frag(acc, qh));
       } else {
 #pragma unroll
         for (int qh = 0; qh < 2; ++qh)
-          frag_put<T, DK>(rec, ti * 32 + rr, ni * 4 + 2 * qh + h, acc_frag<T>(-acc, qh));
+          frag_put<DK>(rec, ti * 32 + rr, ni * 4 + 2 * qh + h, acc_frag(-acc, qh));
       }
     }
   }
@@ -389,11 +379,11 @@ __device__ __forceinline__ int phi_off(int i, int j) {
 }
 
 // LDS of k_gdr_chain: one chunk record.
-template <typename T, int DK, int DV>
+template <int DK, int DV>
 struct ChainLds {
-  typedef GdrRec<T, DK, DV> R;
-  static constexpr size_t bytes = (size_t)R::ELEMS * sizeof(T);
-  static_assert(R::ELEMS * sizeof(T) % (1024 * (gdr::NT / 64)) == 0 && R::UV * sizeof(T) % (1024 * (gdr::NT / 64)) == 0,
+  typedef GdrRec<DK, DV> R;
+  static constexpr size_t bytes = (size_t)R::ELEMS * sizeof(float);
+  static_assert(R::ELEMS * sizeof(float) % (1024 * (gdr::NT / 64)) == 0 && R::UV * sizeof(float) % (1024 * (gdr::NT / 64)) == 0,
                 "every wave copies the same number of KiB");
   static_assert(bytes <= 160 * 1024, "fits LDS");
 };
@@ -413,10 +403,10 @@ constexpr int gdr_xblocks(int cols) { return (cols + 127) / 128; }
 // The chunks of one segment (the whole sequence when ws.P == 1) in order for one (sequence,
 // value head): grid (column blocks, Hv, B * P). With P > 1 the first gdr_xblocks(DK) column
 // blocks carry the columns of Phi, the others those of Psi. Each wave owns 32 columns.
-template <typename T, int DK, int DV>
+template <int DK, int DV>
 __global__ __launch_bounds__(gdr::NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gdr_chain(float* __restrict__ S, const float* __restrict__ gcs, int Hv, int N, GdrWs ws) {
   using namespace gdr;
-  typedef GdrRec<T, DK, DV> R;
+  typedef GdrRec<DK, DV> R;
   constexpr int NKT = DK / 32, XPHI = gdr_xblocks(DK);
   extern __shared__ __align__(16) unsigned char smem[];
   const int P = ws.P;
@@ -434,7 +424,7 @@ __global__ __launch_bounds__(gdr::NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
   const bool active = n0 < ncols;
   const bool from_s = P == 1 || (!phi && seg == 0);
   const bool uses_uv = !phi;
-  const int copy_bytes = (uses_uv ? R::ELEMS : R::UV) * (int)sizeof(T);
+  const int copy_bytes = (uses_uv ? R::ELEMS : R::UV) * 4;
   const int nins = copy_bytes / 1024;  // 1 KiB per wave instruction (64 lanes x 16 bytes)
 
   f32x16 st[NKT];
@@ -455,37 +445,36 @@ __global__ __launch_bounds__(gdr::NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
     }
   }
 
-  auto issue = [&](int c) { gdr_copy_record(ws.rec<T>(seq * NC + c), copy_bytes, smem, wave, nins); };
+  auto issue = [&](int c) { gdr_copy_record(ws.rec<float>(seq * NC + c), copy_bytes, smem, wave, nins); };
 
   issue(c_begin);
   for (int c = c_begin; c < c_end; ++c) {
     const float gc = gcs[seq * NC + c];
     pipe_sync<waitcnt_imm(0, 0)>();  // chunk c has landed for every wave
     if (active) {
-      typedef typename Frag8<T>::type F;
-      const T* Wn = (const T*)smem;
-      const T* Kt = Wn + R::KT;
-      const T* UvT = Wn + R::UV;
+          const float* Wn = (const float*)smem;
+      const float* Kt = Wn + R::KT;
+      const float* UvT = Wn + R::UV;
       // Every fragment of the step is read up front (one block per CU leaves the registers
       // for it), so that LDS latency is paid once per phase, not once per MFMA.
-      F wf[2][NKT][2], uf[2][2];
+      f32x8 wf[2][NKT][2], uf[2][2];
 #pragma unroll
       for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
-          for (int tt = 0; tt < 2; ++tt) wf[tt][kt][q] = frag_get<T, DK>(Wn, tt * 32 + rr, kt * 4 + 2 * q + h);
+          for (int tt = 0; tt < 2; ++tt) wf[tt][kt][q] = frag_get<DK>(Wn, tt * 32 + rr, kt * 4 + 2 * q + h);
       // (read in Phi blocks too, where the buffer's Uv part is stale: the values are not used)
 #pragma unroll
       for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-        for (int q = 0; q < 2; ++q) uf[tt][q] = frag_get<T, C>(UvT, n0 + rr, tt * 4 + 2 * q + h);
-      // U = Uv - W S for the two token tiles (the record holds -W); S enters rounded to T
-      F sb[NKT][2];
+        for (int q = 0; q < 2; ++q) uf[tt][q] = frag_get<C>(UvT, n0 + rr, tt * 4 + 2 * q + h);
+      // U = Uv - W S for the two token tiles (the record holds -W)
+      f32x8 sb[NKT][2];
 #pragma unroll
       for (int kt = 0; kt < NKT; ++kt) {
-        sb[kt][0] = acc_frag<T>(st[kt], 0);
-        sb[kt][1] = acc_frag<T>(st[kt], 1);
+        sb[kt][0] = acc_frag(st[kt], 0);
+        sb[kt][1] = acc_frag(st[kt], 1);
       }
       f32x16 u[2];
 #pragma unroll
@@ -501,20 +490,20 @@ __global__ __launch_bounds__(gdr::NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
 #pragma unroll
           for (int tt = 0; tt < 2; ++tt) mfma_k16(u[tt], wf[tt][kt][q], sb[kt][q]);
       // S = gamma_C S + Kt U
-      F kf[NKT][2][2];
+      f32x8 kf[NKT][2][2];
 #pragma unroll
       for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-          for (int q = 0; q < 2; ++q) kf[kt][tt][q] = frag_get<T, C>(Kt, kt * 32 + rr, tt * 4 + 2 * q + h);
+          for (int q = 0; q < 2; ++q) kf[kt][tt][q] = frag_get<C>(Kt, kt * 32 + rr, tt * 4 + 2 * q + h);
 #pragma unroll
       for (int kt = 0; kt < NKT; ++kt) st[kt] *= gc;
-      F ub[2][2];
+      f32x8 ub[2][2];
 #pragma unroll
       for (int tt = 0; tt < 2; ++tt) {
-        ub[tt][0] = acc_frag<T>(u[tt], 0);
-        ub[tt][1] = acc_frag<T>(u[tt], 1);
+        ub[tt][0] = acc_frag(u[tt], 0);
+        ub[tt][1] = acc_frag(u[tt], 1);
       }
 #pragma unroll
       for (int tt = 0; tt < 2; ++tt)
@@ -546,10 +535,9 @@ __global__ __launch_bounds__(gdr::NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
 
 // S <- Phi_g S + Psi_g for g = 1 .. P-1, from S = Psi_0; grid (column blocks, Hv, B), 32 state
 // columns per wave. The block copies each Phi_g into LDS once (two buffers, the next one in
-// flight) and every wave reads it as the A operand in the k order of the state's accumulators,
-// rounded to the call dtype as the chunk steps round their operands. Psi_g is loaded one step
-// ahead, before the next copy is issued, so that waiting for it never waits for the copy.
-template <typename T, int DK>
+// flight) and every wave reads it as the A operand in the k order of the state's accumulators.
+// Psi_g is loaded one step ahead, before the next copy is issued, so that waiting for it never waits for the copy.
+template <int DK>
 struct MergeLds {
   static constexpr int PHI_BYTES = DK * DK * 4;
   static constexpr size_t bytes = 2 * (size_t)PHI_BYTES;
@@ -557,10 +545,9 @@ struct MergeLds {
   static_assert(PHI_BYTES % (1024 * (gdr::NT / 64)) == 0, "every wave copies the same number of KiB");
 };
 
-template <typename T, int DK, int DV>
+template <int DK, int DV>
 __global__ __launch_bounds__(gdr::NT) void k_gdr_merge(float* __restrict__ S, int Hv, GdrWs ws) {
-  typedef typename Frag8<T>::type F;
-  typedef MergeLds<T, DK> L;
+  typedef MergeLds<DK> L;
   constexpr int NKT = DK / 32;
   extern __shared__ __align__(16) unsigned char smem[];
   const int P = ws.P;
@@ -592,11 +579,11 @@ __global__ __launch_bounds__(gdr::NT) void k_gdr_merge(float* __restrict__ S, in
       gdr_copy_record(ws.phi + (seq * P + g + 1) * DK * DK, L::PHI_BYTES, smem + (size_t)(g & 1) * L::PHI_BYTES,
                       wave, L::PHI_BYTES / 1024);
     if (active) {
-      F sb[NKT][2];
+      f32x8 sb[NKT][2];
 #pragma unroll
       for (int kt = 0; kt < NKT; ++kt) {
-        sb[kt][0] = acc_frag<T>(st[kt], 0);
-        sb[kt][1] = acc_frag<T>(st[kt], 1);
+        sb[kt][0] = acc_frag(st[kt], 0);
+        sb[kt][1] = acc_frag(st[kt], 1);
       }
 #pragma unroll
       for (int kt = 0; kt < NKT; ++kt) st[kt] = ps[kt];
@@ -611,11 +598,11 @@ __global__ __launch_bounds__(gdr::NT) void k_gdr_merge(float* __restrict__ S, in
             const int j = k2 * 32 + 16 * q + 4 * h;
             const f32x4 lo = *(const f32x4*)(Phi + phi_off<DK>(i, j));
             const f32x4 hi = *(const f32x4*)(Phi + phi_off<DK>(i, j + 8));
-            F a;
+            f32x8 a;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              a[e] = from_f32<T>(lo[e]);
-              a[e + 4] = from_f32<T>(hi[e]);
+              a[e] = lo[e];
+              a[e + 4] = hi[e];
             }
             mfma_k16(st[kt], a, sb[k2][q]);
           }
@@ -636,33 +623,33 @@ static void allow_lds_bytes(K kernel, size_t bytes) {
                             (int)bytes);
 }
 
-template <typename T, int DK, int DV>
+template <int DK, int DV>
 static hipError_t gdr_launch(const void* k, const void* v, const float* alpha, const float* beta,
                              float* S, int B, int Hk, int Hv, int N, GdrWs ws, hipStream_t s,
                              const LaunchEvents& ev) {
-  typedef GdrLds<T, DK, DV> LP;
-  typedef ChainLds<T, DK, DV> LC;
+  typedef GdrLds<DK, DV> LP;
+  typedef ChainLds<DK, DV> LC;
   static bool once = [] {
-    allow_lds_bytes(k_gdr_prep<T, DK, DV>, LP::bytes);
-    allow_lds_bytes(k_gdr_chain<T, DK, DV>, LC::bytes);
-    allow_lds_bytes(k_gdr_merge<T, DK, DV>, MergeLds<T, DK>::bytes);
+    allow_lds_bytes(k_gdr_prep<DK, DV>, LP::bytes);
+    allow_lds_bytes(k_gdr_chain<DK, DV>, LC::bytes);
+    allow_lds_bytes(k_gdr_merge<DK, DV>, MergeLds<DK>::bytes);
     return true;
   }();
   (void)once;
   const int NC = (N + gdr::C - 1) / gdr::C;
   record(ev.gdr_prep[0], s);
-  k_gdr_prep<T, DK, DV><<<dim3(NC, Hv, B), gdr::NT, LP::bytes, s>>>(
-      (const T*)k, (const T*)v, alpha, beta, Hk, Hv, N, ws);
+  k_gdr_prep<DK, DV><<<dim3(NC, Hv, B), gdr::NT, LP::bytes, s>>>(
+      (const float*)k, (const float*)v, alpha, beta, Hk, Hv, N, ws);
   record(ev.gdr_prep[1], s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   record(ev.gdr_scan[0], s);
   const int xblocks = ws.P > 1 ? gdr_xblocks(DK) + gdr_xblocks(DV) : gdr_xblocks(DV);
-  k_gdr_chain<T, DK, DV><<<dim3(xblocks, Hv, B * ws.P), gdr::NT, LC::bytes, s>>>(S, ws.gc, Hv, N, ws);
+  k_gdr_chain<DK, DV><<<dim3(xblocks, Hv, B * ws.P), gdr::NT, LC::bytes, s>>>(S, ws.gc, Hv, N, ws);
   if (ws.P > 1) {
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_gdr_merge<T, DK, DV><<<dim3(gdr_xblocks(DV), Hv, B), gdr::NT, MergeLds<T, DK>::bytes, s>>>(S, Hv, ws);
+    k_gdr_merge<DK, DV><<<dim3(gdr_xblocks(DV), Hv, B), gdr::NT, MergeLds<DK>::bytes, s>>>(S, Hv, ws);
   }
   record(ev.gdr_scan[1], s);
   return hipGetLastError();
@@ -729,7 +716,10 @@ GdrWs gdr_layout(void* base, int B, int Hv, int N, int dk, int dv, int dtype) {
   const size_t segs = w.P > 1 ? (size_t)B * Hv * w.P : 0;
   w.phi = p ? (float*)(p + o) : nullptr;  o += al(segs * dk * dk * e);
   w.psi = p ? (float*)(p + o) : nullptr;  o += al(segs * dk * dv * 4);
-  // The size that callers have always been told: full chunk records, whatever the bf16 kernels store.
+  // fp32 needs o. bf16 needs less (kGdrRecBytes a chunk, and no gc) and asks for full chunk records all the
+  // same, at dk = dv = 128 48 KiB a chunk against 6.25: what a write in one segment asked for when the bf16 kernels
+  // stored them (one in several asked for its maps as well), so that sizes kept from then are neither short
+  // nor refused.
   w.bytes = std::max(o, al((size_t)chunks * 64 * (2 * dk + dv) * e) + al((size_t)chunks * 4));
   return w;
 }
@@ -738,10 +728,10 @@ hipError_t launch_delta_rule(const void* k, const void* v, const float* alpha, c
                              float* S, int B, int Hk, int Hv, int N, int dk, int dv, int dtype,
                              GdrWs ws, hipStream_t s, const LaunchEvents& ev) {
   if (dtype == 1) return launch_delta_chunk(k, v, alpha, beta, S, B, Hk, Hv, N, dk, dv, ws, s, ev);
-  if (dk == 128 && dv == 128) return gdr_launch<float, 128, 128>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);
-  if (dk == 128 && dv == 64) return gdr_launch<float, 128, 64>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);
-  if (dk == 64 && dv == 128) return gdr_launch<float, 64, 128>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);
-  return gdr_launch<float, 64, 64>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);
+  if (dk == 128 && dv == 128) return gdr_launch<128, 128>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);
+  if (dk == 128 && dv == 64) return gdr_launch<128, 64>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);
+  if (dk == 64 && dv == 128) return gdr_launch<64, 128>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);
+  return gdr_launch<64, 64>(k, v, alpha, beta, S, B, Hk, Hv, N, ws, s, ev);
 }
 
 }  // namespace dv

@@ -11,11 +11,11 @@ namespace dv {
 
 // Workspace of the chunked delta rule: per (sequence, value head, chunk of 64 tokens) one record (fp32:
 // -W [64][dk], Kt [dk][64] and Uv^T [dv][64] in the fragment order of the chunk kernels; bf16: R and
-// gamma, kGdrRecBytes) and gamma_C (fp32), and per segment of the two-level scan the affine map (Phi
-// in the call dtype, Psi in fp32).
+// gamma, kGdrRecBytes) and, for fp32, gamma_C, and per segment of the two-level scan the affine map (Phi
+// in the call dtype, Psi in fp32). bytes is what callers are asked for, in bf16 more than is used.
 struct GdrWs {
   void* rec_;
-  float* gc;
+  float* gc;      // fp32: gamma_C per chunk
   float* phi;     // per segment: the linear part Phi [dk][dk] of the segment's affine map (call dtype)
   float* psi;     // per segment: the state Psi [dk][dv] it reaches (segment 0: from S)
   int P;          // segments of the two-level scan (1: a single in-order scan)
