@@ -1283,14 +1283,26 @@ __global__ __launch_bounds__(ksplit::NWAVE * 64) void k_attn_ksplit(AttnArgs a, 
 #pragma unroll
     for (int e4 = 0; e4 < 4; ++e4) {
       f32x4 v = *(const f32x4*)(o + e4 * 4);
-      if constexpr (DEC) {
-        // The low parts add nothing to an infinite sum (theirs, with parts of either sign or zero, is NaN).
-        const f32x4 v_low = *(const f32x4*)(o + 16 * MPITCH + e4 * 4);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = __builtin_isfinite(v[u]) ? v[u] + v_low[u] : v[u];
-      }
+      if (DEC) v += *(const f32x4*)(o + 16 * MPITCH + e4 * 4);
 #pragma unroll
       for (int u = 0; u < 4; ++u) out[e4 * 4 + u] += v[u] * sc[w];
+    }
+  }
+  if constexpr (DEC) {
+    // An infinite V entry makes the high sum infinite and the low one, whose parts are of either sign or
+    // zero, NaN: a non-finite output is the high sums' alone.
+    float probe = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) probe = fmaf(out[e], 0.f, probe);
+    if (!(probe == 0.f)) {
+      for (int e = 0; e < 16; ++e) {
+        float x = 0.f;
+        for (int w = 0; w < NWAVE; ++w) {
+          const float* o = red_o + (w * 32 + rrow) * MPITCH + cbase + e;
+          x += (__builtin_isfinite(o[0]) ? o[0] + o[16 * MPITCH] : o[0]) * sc[w];
+        }
+        out[e] = x;
+      }
     }
   }
   if (a.splits == 1) {
