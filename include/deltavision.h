@@ -241,7 +241,8 @@ dv_status dv_kept_visual_kv(const void* E, const void* Dw, const void* Uw, const
  *   scale  softmax scale, finite and > 0, usually 1/sqrt(hd)
  *   ws     split-key partials; may be NULL/0 (then keys are not split). With
  *          dv_text_visual_attention_workspace(...) bytes the call picks its
- *          preferred split; with fewer it uses the largest split that fits.
+ *          preferred split (at some q_pos0 below Nkt - Nq that is more than they
+ *          hold); with fewer it uses the largest split that fits.
  */
 size_t dv_text_visual_attention_workspace(int32_t B, int32_t Hq, int32_t Hkv, int32_t hd,
                                           int32_t Nv, int32_t Nq, int32_t Nkt);
@@ -254,12 +255,13 @@ dv_status dv_text_visual_attention(const void* Q, const void* Kv, const void* Vv
 /*
  * dv_text_visual_attention for callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc). Same arguments, same result
- * bits as dv_text_visual_attention with its recommended workspace, but the key-split partials
+ * bits as dv_text_visual_attention with a workspace that holds its preferred split (the recommended
+ * one does at q_pos0 = Nkt - Nq), but the key-split partials
  * live in a static array of DV_ATTENTION_SCRATCH_BYTES inside the library: each GPU the library
  * runs on holds its own copy until the process ends. The call allocates and frees nothing and
  * clears nothing (every partial is written before it is read). A call whose key split needs
- * more partials than the array holds returns DV_ERR_WORKSPACE without launching (the
- * LLaVA-NeXT-sized prefill, 8 x 128 queries x 32 heads over 2880 visual keys, is one); such
+ * more partials than the array holds returns DV_ERR_WORKSPACE without launching (an fp32 prefill
+ * of 128 queries x 64 heads over 8 kv-heads and 4096 visual keys is one); such
  * calls go through dv_text_visual_attention with a workspace.
  * All calls on one GPU share its array: calls that may overlap on one GPU (different streams,
  * or different threads without ordering) race on it and must be serialised by the caller.

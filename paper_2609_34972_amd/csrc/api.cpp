@@ -590,8 +590,8 @@ dv_status dv_text_visual_attention_noalloc(const void* Q, const void* Kv, const 
                                            int32_t dtype, void* stream) {
   DV_CHECK(check_attention(Q, Kv, Vv, Kt, Vt, O, B, Hq, Hkv, hd, Nv, Nq, Nkt, q_pos0, scale,
                            dtype));
-  // The split dv_text_visual_attention takes with its recommended workspace, so both entry
-  // points give the same bits; a split whose partials exceed the static scratch is refused.
+  // The split dv_text_visual_attention takes with room for it, so both entry points give the
+  // same bits; a split whose partials exceed the static scratch is refused.
   const dv::AttnPlan plan = dv::plan_attention(B, Hq, Hkv, hd, Nv, Nq, Nkt, q_pos0,
                                                dtype == DV_BF16 ? 1 : 0, (size_t)-1);
   const size_t cap = dv::attention_scratch_bytes();

@@ -1065,10 +1065,11 @@ __global__ __launch_bounds__(pp::NWAVE * 64, 1) void k_attn_pp(AttnArgs a, int r
 
 // ------------------------------------------------------------------ key-split prefill (bf16)
 //
-// DEC: one query per sequence and a GQA group of up to 16 heads. Columns 0..15 and 16..31 of the
+// DEC: one query per sequence and a GQA group of 2 to 8 heads. Columns 0..15 and 16..31 of the
 // score product hold the same query rows, so both halves form the same probabilities; the first half
 // multiplies V by their bf16 values and the second by what that rounding left over, and the two
-// outputs are added at the end: O as with fp32 probabilities, from MFMAs that the 32-column product
+// outputs are added at the end: probabilities of about 17 bits (the vector kernel's had 24; error against
+// 64 bits 0.0017 with either), from MFMAs that the 32-column product
 // spends anyway. Bound by the caches' bytes: 28 query heads over 4 kv-heads, 16585 keys a sequence,
 // 92 us a layer for B 16 (5.9 TB/s) where the VALU decode kernel took 339 us.
 //
@@ -1655,7 +1656,7 @@ AttnPlan plan_attention(int B, int Hq, int Hkv, int hd, int Nv, int Nq, int Nkt,
     tiles = cdiv64(max_keys, 16);
   } else {
     const int R = Nq * G;
-    p.nw = R <= 32 ? 1 : (R <= 64 ? 2 : 4);
+    p.nw = R <= 32 ? 1 : (R <= 64 ? 2 : 4);  // (1 and 2: bf16 with hd 64)
     p.row_blocks = (int)cdiv64(R, 32 * p.nw);
     units = (int64_t)n_bg * p.row_blocks;
     tiles = cdiv64(max_keys, 64);
@@ -1718,7 +1719,9 @@ AttnPlan plan_attention(int B, int Hq, int Hkv, int hd, int Nv, int Nq, int Nkt,
 }
 
 size_t attention_workspace(int B, int Hq, int Hkv, int hd, int Nv, int Nq, int Nkt) {
-  // The largest need over both dtypes and every valid q_pos0 (more keys never mean fewer splits).
+  // The larger need of the two dtypes for the longest prefix (q_pos0 = Nkt - Nq). The key-split and the fp32
+  // few-row kernels' room holds their plan for every shorter one; the others' split counts may be higher at
+  // some shorter prefix (56 splits at 31240 keys of one stream, 64 at 28240), which then takes what fits.
   const AttnPlan p0 = plan_attention(B, Hq, Hkv, hd, Nv, Nq, Nkt, Nkt - Nq, 0, (size_t)-1);
   const AttnPlan p1 = plan_attention(B, Hq, Hkv, hd, Nv, Nq, Nkt, Nkt - Nq, 1, (size_t)-1);
   return std::max(p0.ws_room, p1.ws_room);

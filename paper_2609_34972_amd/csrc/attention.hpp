@@ -40,7 +40,7 @@ struct AttnPlan {
   int splits;          // key splits merged by a log-sum-exp combine
   int keys_per_split;  // decode and the generic prefill: a multiple of their 64-key tile
   size_t ws_needed;    // bytes of partials for this plan
-  size_t ws_room;      // bytes that hold the plan of this shape for any smaller q_pos0 too
+  size_t ws_room;      // ws_needed, or for ksplit and f32rows what holds their plan for any smaller q_pos0 too
 };
 
 AttnPlan plan_attention(int B, int Hq, int Hkv, int hd, int Nv, int Nq, int Nkt, int q_pos0,

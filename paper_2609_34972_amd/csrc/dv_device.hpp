@@ -57,7 +57,10 @@ __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >>
 __device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x)); }
 // silu for results that are rounded to bf16: the hardware's reciprocal (1 ulp in fp32) in place of the
 // division, whose scaling and correction are ten instructions an element (down projection of the Qwen2.5-VL
-// video, 235 M elements a call).
+// video, 235 M elements a call: 1387 -> 1325 us). Of the 65280 finite bf16 inputs one rounds the other way
+// (5.9375, next to a tie) and -88.5 to -87.5 give -0, as those below do with either (silu is above -1e-36
+// there); Z's error against 64 bits is the same (0.00167 to 0.00168 at 64 to 16384 tokens). The recurrent
+// adapter's k_reduce_act, which waits for its partials, keeps the division.
 __device__ __forceinline__ float silu_rcp(float x) { return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
 __device__ __forceinline__ float gelu(float x) { return 0.5f * x * erfcf(-x * 0.70710678118654752f); }
 
