@@ -1,5 +1,5 @@
 """GPU parity of the fp32 kernels for small calls: the build in 16 x 16 tiles (token counts around a tile,
-reductions shorter than the waves that split them, several layers in a tile row) and attention in blocks of
+reductions of less than one and of several batches of loads, several layers in a tile row) and attention in blocks of
 16 rows whose waves share out 16-key tiles (fewer tiles than waves, ragged and masked tiles, no visual keys,
 a chunk of a longer prompt, key splits). At or below the launch rule's line and just above it, where the
 64 x 64-tile kernels run, and, for the build, both sides compared to the bit. Parity bar for fp32 (1e-4) against
